@@ -205,7 +205,7 @@ q4nx_status q4nx_gemm(int64_t M, int64_t N, int64_t K, const uint16_t* d_X, cons
  * the dequantization engine writes the bf16 weights that the MM then consumes
  * (Sec. 3.1.1 and 3.1.2): q4nx_dequant(blob, Q4NX_BF16) followed by this call.
  * The arithmetic is that of q4nx_gemm (bf16 x bf16 products on the matrix
- * cores, float32 sums over K in increasing order), so with W from
+ * cores, float32 sums over K in an order fixed by M, N and K), so with W from
  * q4nx_dequant the result equals q4nx_gemm on the packed matrix bit for bit.
  *   d_X : device, row-major [M][K] bf16, 16-byte aligned
  *   d_W : device, row-major [N][K] bf16, 16-byte aligned (the caller owns it)

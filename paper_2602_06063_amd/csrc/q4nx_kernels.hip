@@ -11,6 +11,8 @@
 // the lane's group sits at index 8r + c = 64t + l of the block's tables.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <string>
 #include <vector>
@@ -792,8 +794,9 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void gemv_stream_kernel(const G
 // paper's prefill dequantizes to bf16 before the MM).  LDS rows are padded to
 // 72 elements (144 B) so that the 16-byte fragment reads of 8 consecutive
 // rows, and the 16-byte tile writes, hit distinct banks.  Each output is the
-// float32 sum of its MFMA chain over K in increasing order, so every kernel
-// and every tile shape gives the same bits.  MXFP4-variant weights take the
+// float32 sum of its MFMA chain over K in increasing order, so these kernels
+// and all their tile shapes give the same bits.  (Where gemm_ks_kernel, below,
+// takes a product, it sums in another fixed order.)  MXFP4-variant weights take the
 // same path with the Eq. 3 step replaced by the exact FP4 x scale conversion.
 constexpr int kBK = 64;
 constexpr int kLdsStride = kBK + 8;  // bf16 elements per LDS row
@@ -1844,6 +1847,250 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_kernel(
     }
 }
 
+// ---- few rows: K split over the waves of a workgroup -------------------------
+// For products with too few tiles of the kernels above to fill the CUs: short
+// prompts, batches of decoding users, the last chunk of a prompt.  There the
+// latency of the operand loads bounds the general kernel (one K step of a
+// 128 x 64 tile took 0.7 us with 8 us of matrix work in 256 of them).  A
+// workgroup owns 16 MT rows x 16 NT outputs and all of K; its W waves deal the
+// 128-column units of K out among themselves (unit u to wave u % W), each wave
+// computing the whole tile over its units without a barrier, and the W partial
+// tiles are added in wave order through LDS at the end.  Splitting K rather
+// than the tile over the waves keeps every X fragment and every dequantized
+// weight in one wave, so nothing is read or converted twice, and all of a CU's
+// waves have loads in flight.
+// A unit of W (half a block) and of X go through the wave's own LDS slot:
+// loaded with whole 64-byte (codes) and 256-byte (X) row pieces, written with
+// padded rows (272 bytes for X, 80 for codes: conflict-free), and read back in
+// the operand layout of v_mfma_f32_16x16x32_bf16: lane l holds row l % 16 and
+// group l / 16 of the unit, whose 8-column runs are the fragments of four
+// MFMAs.  (Loading the fragments straight from memory, 16 bytes per row and
+// lane, took 20 instead of 16 us on a 32-row tile: the address unit handles
+// such a load at a quarter of the rate.)  A wave's LDS instructions are
+// carried out in order, so one slot per wave is enough.
+// Measured on MI355X, Q4NX weights (general kernel's plan -> this one, us):
+// Gemma3-1B at 16 rows q/k/v 14.7 -> 4.2, o 13.4 -> 4.0, gate/up 16.4 -> 7.1,
+// down 67.5 -> 9.0; 4B at 77 rows 29.0 -> 9.7, 23.9 -> 6.9, 41.5 -> 30.9,
+// 100 -> 18.4.  Whole calls through q4nx_gemm_ex: eight 1B layers at 16 rows
+// 869 -> 278 us (then bound by the caller), four 4B layers at 77 rows 816 ->
+// 269 us, two at 512 rows 541 -> 327 us.
+// The order of every sum is fixed by M, N and K, and is the same for the three
+// weight operands, so they agree bit for bit on the same bf16 weights.
+constexpr int kKsUnit = 128;              // columns of K per unit
+constexpr int kKsRow = 2 * kKsUnit + 16;  // LDS bytes per staged bf16 row
+constexpr int kKsCodeRow = 80;            // LDS bytes per staged row of codes
+
+// One unit of W as loaded.  Packed: codes of 16 rows per load (4 lanes per
+// row), scale and offset of row l % 16, group l / 16.  bf16: 4 rows per load.
+template <int NT, int WF>
+struct KsUnit {
+  u32x4 q[NT];
+  uint32_t s[NT], m[NT];
+};
+template <int NT>
+struct KsUnit<NT, kWBf16> {
+  u32x4 q[4 * NT];
+};
+
+template <int MT, int NT, int WF>
+constexpr int ks_wave_lds() {
+  return 16 * MT * kKsRow + 16 * NT * (WF == kWBf16 ? kKsRow : kKsCodeRow);
+}
+template <int MT, int NT, int W, int WF>
+constexpr int ks_lds_bytes() {
+  return W * std::max(ks_wave_lds<MT, NT, WF>(), MT * NT * 1024);
+}
+
+// Tiles of 16 and more blocks take the whole register file (one wave per SIMD).
+template <int MT, int NT, int W, int WF>
+__global__ __launch_bounds__(64 * W, MT * NT >= 16 || MT > 4 ? 1 : 2) void gemm_ks_kernel(
+    const uint16_t* __restrict__ X, const uint8_t* __restrict__ wsrc, void* __restrict__ Y, int M, int N, int K,
+    int ldy, int KB, int NS, int tiles_n, int y_bf16) {
+  constexpr int kBB = wblock_bytes<WF>();
+  constexpr int kXI = 4 * MT;                 // X loads (4 rows each) per unit
+  constexpr uint32_t kPastEnd = 0x7FFFFFF0u;  // beyond every descriptor: loads return 0
+  extern __shared__ __attribute__((aligned(16))) uint16_t gl[];
+
+  int bm, bn;
+  gemm_tile_of(blockIdx.x, gridDim.x, tiles_n, bm, bn);
+  const int m0 = bm * 16 * MT, n0 = bn * 16 * NT;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 15, h = lane >> 4;
+  uint8_t* const xs = reinterpret_cast<uint8_t*>(gl) + wave * ks_wave_lds<MT, NT, WF>();
+  uint8_t* const ws = xs + 16 * MT * kKsRow;
+
+  const int rows_x = min(16 * MT, M - m0);
+  const __amdgpu_buffer_rsrc_t rsx = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(X + (size_t)m0 * K), (short)0, rows_x * K * 2, 0x00020000);
+  // Packed W: the strips that hold rows n0 .. n0 + 16 NT - 1 (n0 may lie in the middle of one).
+  const int s0 = n0 >> 5, r0 = n0 & 31, nst = min((r0 + 16 * NT + 31) >> 5, NS - s0), rows_w = min(16 * NT, N - n0);
+  const __amdgpu_buffer_rsrc_t rsw =
+      WF != kWBf16 ? __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(wsrc + (size_t)s0 * KB * kBB), (short)0,
+                                                       nst * KB * kBB, 0x00020000)
+                   : __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(wsrc + (size_t)n0 * K * 2), (short)0,
+                                                       rows_w * K * 2, 0x00020000);
+  // Rows past M and strips past the matrix read 0 (their outputs are never stored).
+  uint32_t vx[kXI];
+#pragma unroll
+  for (int i = 0; i < kXI; ++i) {
+    const int row = h + 4 * i;
+    vx[i] = row < rows_x ? (uint32_t)(row * K + 8 * c) * 2 : kPastEnd;
+  }
+  constexpr int kVW = WF == kWBf16 ? 4 * NT : NT;
+  uint32_t vw[kVW], vs[NT];
+  if constexpr (WF != kWBf16) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int rq = r0 + 16 * t + (lane >> 2), rs = r0 + 16 * t + c;  // rows from strip s0's first
+      vw[t] = (rq >> 5) < nst ? (uint32_t)((rq >> 5) * KB * kBB + 128 * (rq & 31) + 16 * (lane & 3)) : kPastEnd;
+      vs[t] = (rs >> 5) < nst
+                  ? (uint32_t)((rs >> 5) * KB * kBB + kCodeBytes + (WF == kWMX ? 1 : 2) * (8 * (rs & 31) + h))
+                  : kPastEnd;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4 * NT; ++i) {
+      const int row = h + 4 * i;
+      vw[i] = row < rows_w ? (uint32_t)(row * K + 8 * c) * 2 : kPastEnd;
+    }
+  }
+  // Units of this wave: wave + W i for i < nu.
+  const int units = (K + kKsUnit - 1) / kKsUnit;
+  const int nu = wave < units ? (units - wave + W - 1) / W : 0;
+
+  // Loads of the wave's i-th unit.  Columns past K, and units past the wave's
+  // last, read 0 (with the scalar offset inside the descriptor).
+  auto load_x = [&](u32x4 (&R)[kXI], int i) {
+    const int k0 = (wave + W * i) * kKsUnit;
+    const bool on = i < nu;  // uniform over the wave
+    const uint32_t past = on && k0 + 8 * c < K ? 0 : kPastEnd;
+    const int so = on ? 2 * k0 : 0;
+#pragma unroll
+    for (int j = 0; j < kXI; ++j)
+      R[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsx, vx[j] | past, so, 0));
+  };
+  auto load_w = [&](KsUnit<NT, WF>& R, int i) {
+    const int u = wave + W * i, k0 = u * kKsUnit;
+    const bool on = i < nu;
+    if constexpr (WF == kWBf16) {
+      const uint32_t past = on && k0 + 8 * c < K ? 0 : kPastEnd;
+      const int so = on ? 2 * k0 : 0;
+#pragma unroll
+      for (int j = 0; j < 4 * NT; ++j)
+        R.q[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsw, vw[j] | past, so, 0));
+    } else {
+      const uint32_t past = on ? 0 : kPastEnd;
+      const int so = on ? (u >> 1) * kBB : 0, hb = u & 1;  // block, half of it
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        R.q[t] = __builtin_bit_cast(u32x4,
+                                    __builtin_amdgcn_raw_buffer_load_b128(rsw, (vw[t] + 64 * hb) | past, so, kNtLoad));
+        if constexpr (WF == kWMX) {
+          R.s[t] = __builtin_amdgcn_raw_buffer_load_b8(rsw, (vs[t] + 4 * hb) | past, so, kNtLoad);
+        } else {
+          R.s[t] = __builtin_amdgcn_raw_buffer_load_b16(rsw, (vs[t] + 8 * hb) | past, so, kNtLoad);
+          R.m[t] = __builtin_amdgcn_raw_buffer_load_b16(rsw, (vs[t] + kScaleBytes + 8 * hb) | past, so, kNtLoad);
+        }
+      }
+    }
+  };
+
+  f32x4 acc[MT][NT];
+#pragma unroll
+  for (int a = 0; a < MT; ++a)
+#pragma unroll
+    for (int b = 0; b < NT; ++b) acc[a][b] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+
+  u32x4 Xr[kXI];
+  KsUnit<NT, WF> W0, W1;
+  load_w(W0, 0);
+  load_x(Xr, 0);
+  load_w(W1, 1);
+  // One unit: its X and W registers go to LDS and are reloaded at once, then
+  // the MFMAs from LDS.
+  auto unit = [&](KsUnit<NT, WF>& Wr, int i) {
+#pragma unroll
+    for (int j = 0; j < kXI; ++j) *reinterpret_cast<u32x4*>(xs + (h + 4 * j) * kKsRow + 16 * c) = Xr[j];
+    float d[NT], mo[NT];
+    if constexpr (WF == kWBf16) {
+#pragma unroll
+      for (int j = 0; j < 4 * NT; ++j) *reinterpret_cast<u32x4*>(ws + (h + 4 * j) * kKsRow + 16 * c) = Wr.q[j];
+    } else {
+      // A group past K is scale and offset 0 whatever the padding holds.
+      const bool in_k = (wave + W * i) * kKsUnit + kGroup * h < K;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        *reinterpret_cast<u32x4*>(ws + (16 * t + (lane >> 2)) * kKsCodeRow + 16 * (lane & 3)) = Wr.q[t];
+        if constexpr (WF == kWMX) {
+          d[t] = in_k ? e8m0_f32(Wr.s[t]) : 0.0f;
+        } else {
+          d[t] = in_k ? bf16_to_f32(Wr.s[t]) * 512.0f : 0.0f;
+          mo[t] = in_k ? bf16_to_f32(Wr.m[t]) : 0.0f;
+        }
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_sched_barrier(0);
+    load_x(Xr, i + 1);
+    load_w(Wr, i + 2);
+    u32x4 q[NT];
+    if constexpr (WF != kWBf16) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) q[t] = *reinterpret_cast<const u32x4*>(ws + (16 * t + c) * kKsCodeRow + 16 * h);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      bf16x8 A[MT];
+#pragma unroll
+      for (int a = 0; a < MT; ++a)
+        A[a] = *reinterpret_cast<const bf16x8*>(xs + (16 * a + c) * kKsRow + 64 * h + 16 * u);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        u32x4 b;
+        if constexpr (WF == kWQ4NX) b = dequant8_bf16(q[t][u], d[t], mo[t]);
+        else if constexpr (WF == kWMX) b = mx8_bf16(q[t][u], d[t]);
+        else b = *reinterpret_cast<const u32x4*>(ws + (16 * t + c) * kKsRow + 64 * h + 16 * u);
+#pragma unroll
+        for (int a = 0; a < MT; ++a)
+          acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[a], __builtin_bit_cast(bf16x8, b), acc[a][t], 0, 0, 0);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  };
+  int i = 0;
+  for (; i + 1 < nu; i += 2) {
+    unit(W0, i);
+    unit(W1, i + 1);
+  }
+  if (i < nu) unit(W0, i);
+
+  // Add the waves' partial tiles in wave order.  Element e of lane l of block
+  // (a, t) is row 16a + 4h + e, column 16t + c.
+  f32x4* const red = reinterpret_cast<f32x4*>(gl);
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < MT; ++a)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) red[((wave * MT + a) * NT + t) * 64 + lane] = acc[a][t];
+  __syncthreads();
+  for (int sl = wave; sl < MT * NT; sl += W) {
+    f32x4 v = red[sl * 64 + lane];
+#pragma unroll
+    for (int p = 1; p < W; ++p) v += red[(p * MT * NT + sl) * 64 + lane];
+    const int col = n0 + 16 * (sl % NT) + c, row = m0 + 16 * (sl / NT) + 4 * h;
+    if (col >= N) continue;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (row + e < M) {
+        if (y_bf16)
+          static_cast<uint16_t*>(Y)[(size_t)(row + e) * ldy + col] = f32_to_bf16_bits(v[e]);
+        else
+          static_cast<float*>(Y)[(size_t)(row + e) * ldy + col] = v[e];
+      }
+  }
+}
+
 // ---- launch planning ----------------------------------------------------------
 // Tile shapes: 0 = 256 x 256 (gemm256_kernel; the general kernel past
 // kWideMaxK), 1 = 256 x 128 (gemm256x128_kernel; the general kernel with a K
@@ -1996,18 +2243,78 @@ static size_t plan_work_bytes(const GemmRegion* plan, int count) {
 constexpr double kDequantLaunchUs = 3.0, kDequantBytesPerUs = 5.5e6;
 constexpr double kFusedExtraWide = 0.20, kFusedExtraSmall = 0.14;
 
+// Tiles of gemm_ks_kernel (16 mt rows x 16 nt outputs, K over `waves` waves).
+// unit_us: time of one 128-column unit of one tile on a CU, fitted on MI355X
+// from launches of one tile per CU over K = 2048 .. 21504 (Q4NX weights); a
+// tile costs kKsTileUs more for its first loads and final sum, a launch
+// kKsLaunchUs.
+struct KsTile {
+  int mt, nt, waves;
+  float unit_us;
+};
+constexpr KsTile kKsTiles[] = {{1, 1, 8, 0.09f}, {1, 2, 4, 0.15f}, {2, 2, 4, 0.17f}, {3, 2, 4, 0.25f},
+                               {2, 4, 4, 0.31f}, {3, 4, 4, 0.47f}, {4, 4, 4, 0.58f}, {5, 4, 4, 0.60f},
+                               {6, 4, 4, 0.72f}, {8, 4, 4, 0.85f}};
+constexpr int kKsConfigs = (int)(sizeof(kKsTiles) / sizeof(kKsTiles[0]));
+constexpr double kKsLaunchUs = 3.2, kKsTileUs = 1.2;
+constexpr int64_t kKsMaxTiles = 16384;  // beyond it the chip is full many times over
+// What a full round of the other kernels' tiles takes, for the comparison:
+// round_us below overestimates small launches, whose plans it only ranks.
+// Measured on MI355X at K = 1152 .. 21504.
+constexpr double kTileFixedUs = 16.0, kTilePerKUs = 0.0237;
+constexpr double kTileCost[4] = {0.88, 0.55, 0.50, 0.38};
+
+// Index of the gemm_ks_kernel tile to use for a product that the plan would
+// otherwise compute, or -1 where the plan is estimated to be faster.  Only M,
+// N, K, the device and whether there is a workspace count, so the three
+// weight operands always take the same sums.
+static int ks_choose(int64_t M, int64_t N, int64_t K, int cus, const GemmRegion* plan, int count) {
+  if (K >= kWideMaxK) return -1;
+  double best = 0.0;
+  for (int i = 0; i < count; ++i) {
+    const GemmTile& t = kGemmTiles[plan[i].tile];
+    const double tiles = (double)ceil_div(plan[i].M, t.bm) * (double)ceil_div(plan[i].N, t.bn) * plan[i].ks;
+    const double k = (double)K / plan[i].ks;
+    best += std::ceil(tiles / cus) * kTileCost[plan[i].tile] * (kTileFixedUs + kTilePerKUs * k);
+    if (plan[i].ks > 1)
+      best += kSumLaunchUs + (4.0 * plan[i].ks + 4.0) * (double)plan[i].M * (double)plan[i].N / kSumBytesPerUs;
+  }
+  int pick = -1;
+  const double units = (double)ceil_div(K, kKsUnit);
+  for (int i = 0; i < kKsConfigs; ++i) {
+    const KsTile& t = kKsTiles[i];
+    const int64_t tiles = ceil_div(M, 16 * t.mt) * ceil_div(N, 16 * t.nt);
+    if (tiles > kKsMaxTiles) continue;
+    // Small tiles share a CU, so a part of a round costs its share.
+    double load = std::max(1.0, (double)tiles / cus);
+    if (t.mt * t.nt >= 16) load = std::ceil(load);
+    const double c = kKsLaunchUs + load * (kKsTileUs + units * t.unit_us);
+    if (c < best) {
+      best = c;
+      pick = i;
+    }
+  }
+  return pick;
+}
+
 struct GemmChoice {
   GemmRegion plan[2];
   int count;
+  int ks;             // index into kKsTiles: one launch of gemm_ks_kernel instead of the plan; -1: the plan
   bool two_phase;
   size_t w_bytes;     // bf16 W at the start of the workspace (two-phase only)
   size_t part_bytes;  // split-K partial products after it
 };
 
+// (The workspace a call asks for is that of the plan, also where gemm_ks_kernel
+// takes the product and leaves it unused: callers size and keep workspaces by
+// it.)
 static GemmChoice gemm_choose(int wf, int64_t M, int64_t N, int64_t K, bool have_work) {
   GemmChoice c{};
   double est_us = 0.0;
-  c.count = gemm_plan(M, N, K, device_cus(), have_work, c.plan, &est_us);
+  const int cus = device_cus();
+  c.count = gemm_plan(M, N, K, cus, have_work, c.plan, &est_us);
+  c.ks = ks_choose(M, N, K, cus, c.plan, c.count);
   c.part_bytes = plan_work_bytes(c.plan, c.count);
   const double deq_us = kDequantLaunchUs + (kBlockBytes / (double)(kBlockRows * kBlockCols) + 2.0) * (double)N *
                                                (double)K / kDequantBytesPerUs;
@@ -2062,6 +2369,43 @@ static q4nx_status launch_gemm256x128(int64_t M, int64_t N, int64_t K, const uin
                      static_cast<const uint8_t*>(blob), Y, (int)M, (int)N, (int)K, (int)ldy,
                      (int)ceil_div(K, kBlockCols), (int)ceil_div(N, kBlockRows), (int)tiles_n, y_bf16);
   return Q4NX_OK;
+}
+
+template <int MT, int NT, int W, int WF>
+static q4nx_status launch_ks(int64_t M, int64_t N, int64_t K, const uint16_t* X, const void* w, void* Y, int y_bf16,
+                             hipStream_t stream) {
+  auto kern = gemm_ks_kernel<MT, NT, W, WF>;
+  constexpr int lds = ks_lds_bytes<MT, NT, W, WF>();
+  static_assert(lds <= 160 * 1024, "LDS of a CU");
+  static LdsReservation lds_res;
+  if (!lds_res.ensure(reinterpret_cast<const void*>(kern), lds))
+    return fail(Q4NX_ERR_HIP, "q4nx_gemm: cannot reserve LDS");
+  const int64_t tiles_n = ceil_div(N, 16 * NT), tiles_m = ceil_div(M, 16 * MT);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_n * tiles_m)), dim3(64 * W), lds, stream, X,
+                     static_cast<const uint8_t*>(w), Y, (int)M, (int)N, (int)K, (int)N,
+                     (int)ceil_div(K, kBlockCols), (int)ceil_div(N, kBlockRows), (int)tiles_n, y_bf16);
+  return Q4NX_OK;
+}
+
+// The product by gemm_ks_kernel with tile `cfg` of kKsTiles.  bf16 weights
+// take more LDS per unit: their tiles stop at 64 x 64 (the same waves, hence
+// the same bits).
+template <int WF>
+static q4nx_status launch_ks_config(int cfg, int64_t M, int64_t N, int64_t K, const uint16_t* X, const void* w,
+                                    void* Y, int y_bf16, hipStream_t stream) {
+  constexpr bool big = WF != kWBf16;
+  switch (cfg) {
+    case 0: return launch_ks<1, 1, 8, WF>(M, N, K, X, w, Y, y_bf16, stream);
+    case 1: return launch_ks<1, 2, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
+    case 2: return launch_ks<2, 2, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
+    case 3: return launch_ks<3, 2, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
+    case 4: return launch_ks<2, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
+    case 5: return launch_ks<3, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
+    case 6: return launch_ks<4, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
+    case 7: return launch_ks<big ? 5 : 4, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
+    case 8: return launch_ks<big ? 6 : 4, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
+    default: return launch_ks<big ? 8 : 4, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
+  }
 }
 
 // One region of the output: X rows m0.., W rows n0.. (strips n0/32.. of a
@@ -2133,7 +2477,9 @@ static q4nx_status gemm_entry(int64_t M, int64_t N, int64_t K, const uint16_t* d
   const int y_bf16 = y_dtype == Q4NX_BF16;
   float* part = reinterpret_cast<float*>(static_cast<uint8_t*>(d_work) + c.w_bytes);
   q4nx_status st = Q4NX_OK;
-  if (c.two_phase) {
+  if (c.ks >= 0) {
+    st = launch_ks_config<WF>(c.ks, M, N, K, d_X, d_W, d_Y, y_bf16, stream);
+  } else if (c.two_phase) {
     const int64_t KB = ceil_div(K, kBlockCols), nblocks = ceil_div(N, kBlockRows) * KB;
     hipLaunchKernelGGL(dequant_kernel<kWQ4NX>, dim3((unsigned)std::min<int64_t>(nblocks, int64_t(1) << 20)),
                        dim3(256), 0, stream, static_cast<const uint8_t*>(d_W), N, K, KB, nblocks, d_work, 1);

@@ -275,3 +275,48 @@ def test_gemm_ex_split_repeats_with_workspace_cleared(q4):
         q4.q4nx_gemm_ex(q4.Q4NX_WEIGHTS_Q4NX, M, N, K, X, blob, y, work=work)
     torch.cuda.synchronize()
     assert all(torch.equal(y.view(torch.int32), ref.view(torch.int32)) for y in outs)
+
+
+# One shape per tile of the kernel that splits K over a workgroup's waves
+# (q4nx_gemm's choice for few rows on a 256-CU device), each with ragged M and
+# N (the last tile of either may hold a few rows or outputs, N not a multiple
+# of a strip) and a K that ends inside a 128-column unit; then K of one group,
+# one unit, and many units.
+FEW_ROWS = [(16, 100, 1184), (1, 6001, 1184), (34, 3001, 1184), (47, 6001, 1184), (145, 2501, 1184),
+            (67, 8001, 1184), (193, 4001, 1184), (145, 6001, 1184), (163, 6001, 1184), (193, 6001, 1184),
+            (3, 40, 32), (17, 33, 128), (77, 2560, 10272)]
+
+
+@pytest.mark.parametrize("M,N,K", FEW_ROWS)
+def test_gemm_few_rows(q4, M, N, K):
+    """Float32 and bf16 outputs against the float64 product of the bf16
+    weights (within 1e-5 of sum |x w|: float32 sums of exact products, over
+    sampled rows), nothing written past M x N, and the same bits from the
+    packed matrix, the MXFP4 variant and the bf16 weights they dequantize to."""
+    _say("gemm few rows", M, N, K)
+    codes, s, o = gen_weights(N, K, seed=M + N)
+    blob = dev_u8(q4.q4nx_pack(codes, s, o))
+    Xh = gen_activations((M, K), seed=K + M)
+    X = dev_bf16(Xh)
+    W = torch.empty((N, K), dtype=torch.bfloat16, device="cuda")
+    Y = [torch.full((M * N + 64,), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2)]
+    q4.q4nx_gemm(M, N, K, X, blob, Y[0])
+    q4.q4nx_dequant(blob, N, K, W)
+    q4.q4nx_gemm_bf16(M, N, K, X, W, Y[1])
+    Yb = torch.full((M * N + 64,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    q4.q4nx_gemm(M, N, K, X, blob, Yb)
+    torch.cuda.synchronize()
+    assert torch.equal(Y[0].view(torch.int32), Y[1].view(torch.int32))
+    assert torch.equal(Yb[:M * N].view(torch.int16), Y[0][:M * N].bfloat16().view(torch.int16))
+    assert torch.isnan(Y[0][M * N:]).all() and torch.isnan(Yb[M * N:]).all()
+    rows = np.unique(np.concatenate([np.arange(min(M, 4)), M - 1 - np.arange(min(M, 20))]))
+    w16 = oracle.bf16_to_f32(oracle.f32_to_bf16(oracle.dequant_f32(codes, s, o)))
+    err = np.abs(host_f32(Y[0])[:M * N].reshape(M, N)[rows].astype(np.float64) - oracle.gemm_f64(Xh[rows], w16))
+    assert (err <= 1e-5 * oracle.abs_bound(Xh[rows], w16) + 1e-6).all()
+    mcodes, msc = gen_mx_weights(N, K, seed=K, mode="edge")
+    mblob = dev_u8(q4.q4nx_mx_pack(mcodes, msc))
+    q4.q4nx_mx_gemm(M, N, K, X, mblob, Y[0])
+    q4.q4nx_mx_dequant(mblob, N, K, W)
+    q4.q4nx_gemm_bf16(M, N, K, X, W, Y[1])
+    torch.cuda.synchronize()
+    assert torch.equal(Y[0].view(torch.int32), Y[1].view(torch.int32))
