@@ -441,6 +441,31 @@ def test_quantize_bit_exact(q4, N, K, kind):
     assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("seed", [0, 1])
+def test_quantize_near_ties_bit_exact(q4, seed):
+    """Weights on and within a few float32 steps of the midpoints between two
+    levels, at every size of the offset against the scale (2^-3 to 2^24 times,
+    where the levels repeat): the codes that the rounded quotient cannot
+    decide, and groups of one value."""
+    N, K = 96, 1056
+    _say("quantize near ties", seed)
+    rng = np.random.default_rng(seed)
+    G = K // 32
+    d = np.exp2(rng.integers(-20, 20, (N, G, 1))) * rng.integers(128, 256, (N, G, 1)) / 256.0
+    m = d * np.exp2(rng.uniform(-3, 24, (N, G, 1))) * rng.choice([-1.0, 1.0], (N, G, 1))
+    pos = rng.integers(0, 31, (N, G, 32)) / 2.0 + rng.integers(-3, 4, (N, G, 32)) * np.exp2(rng.integers(-26, -10, (N, G, 32)))
+    W = (m + d * pos).astype(np.float32)
+    W[:, :, 0] = m[:, :, 0]
+    W[:, :, 1] = (m + 15 * d)[:, :, 0]
+    W = np.nextafter(W, W + rng.choice([-1.0, 0.0, 1.0], W.shape).astype(np.float32))
+    W[rng.random((N, G)) < 0.05] = np.float32(0.75)
+    W = np.ascontiguousarray(W.reshape(N, K), dtype=np.float32)
+    blob = torch.full((q4.q4nx_packed_size(N, K),), 0xAB, dtype=torch.uint8, device="cuda")
+    q4.q4nx_quantize(torch.from_numpy(W).cuda(), N, K, blob)
+    torch.cuda.synchronize()
+    assert np.array_equal(blob.cpu().numpy(), oracle.pack(*oracle.quantize(W)))
+
+
 # ----------------------------------------------------------------- measurement aid
 def test_stream_read_folds_every_word(q4):
     """q4nx_stream_read reads every 16-byte piece exactly once: its per-wave
