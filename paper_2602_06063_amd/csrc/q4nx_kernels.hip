@@ -173,67 +173,55 @@ constexpr int wblock_bytes() {
 // ---------------------------------------------------------------------------
 // q4nx_dequant / q4nx_mx_dequant: every weight, written row-major [N][K]
 // ---------------------------------------------------------------------------
-// One workgroup of 256 threads per block, 32 lanes per block row: lane j of a
-// row handles columns 8j..8j+7 (one 32-bit word of codes, in group j/4), so a
-// row's 32 lanes read 128 contiguous bytes of codes and write 512 (bf16) or
-// 1024 (float32) contiguous bytes -- every store instruction writes whole
-// lines.  Eight rows per pass, four passes per block.  (A lane per group, 64
-// bytes of output per lane, writes a quarter of every line per instruction and
-// ran at a fifth of this speed.)
-template <int F>
+// One workgroup of 256 threads per block.  Every store is 16 bytes per lane and
+// every store instruction writes whole lines: bf16, 32 lanes per block row, lane
+// j the columns 8j..8j+7 (one 32-bit word of codes, in group j/4; 512 bytes a
+// row), eight rows per pass and four passes; float32, 64 lanes per row, lane j
+// the columns 4j..4j+3 (a 16-bit half of a word, in group j/8; 1024 bytes a
+// row), four rows per pass and eight passes.  (A lane per group, 64 bytes of
+// output per lane, writes a quarter of every line per instruction and ran at
+// a fifth of this speed; float32 as two 16-byte halves of 32 bytes per lane
+// wrote half of every line: 21504 x 5376 in 142 us.)
+template <int F, bool BF16>
 __global__ __launch_bounds__(256) void dequant_kernel(const uint8_t* __restrict__ blob, int64_t N, int64_t K,
-                                                      int64_t KB, int64_t nblocks, void* __restrict__ W,
-                                                      int w_bf16) {
+                                                      int64_t KB, int64_t nblocks, void* __restrict__ W) {
   constexpr int kBytes = wblock_bytes<F>();
-  const int lr = threadIdx.x >> 5, j = threadIdx.x & 31;
+  constexpr int kCols = BF16 ? 8 : 4, kLanes = kBlockCols / kCols, kRows = 256 / kLanes;  // per lane, row and pass
+  const int lr = threadIdx.x / kLanes, j = threadIdx.x % kLanes;
   for (int64_t b = blockIdx.x; b < nblocks; b += gridDim.x) {
     const int64_t i = b / KB, jb = b - i * KB;
-    const int64_t k = jb * kBlockCols + 8 * j;
+    const int64_t k = jb * kBlockCols + kCols * j;
     if (k >= K) continue;  // K is a multiple of 32: whole groups lie past K
     const uint8_t* blk = blob + b * kBytes;
 #pragma unroll
-    for (int pass = 0; pass < 4; ++pass) {
-      const int r = 8 * pass + lr;
+    for (int pass = 0; pass < kBlockRows / kRows; ++pass) {
+      const int r = kRows * pass + lr;
       const int64_t n = i * kBlockRows + r;
       if (n >= N) break;
-      const uint32_t codes = *reinterpret_cast<const uint32_t*>(blk + 128 * r + 4 * j);
-      const int gi = kGroupsPerRow * r + (j >> 2);
-      u32x4 ob;
-      float of[8];
+      uint32_t codes;
+      if constexpr (BF16) codes = *reinterpret_cast<const uint32_t*>(blk + 128 * r + 4 * j);
+      else codes = *reinterpret_cast<const uint16_t*>(blk + 128 * r + 2 * j);
+      const int gi = kGroupsPerRow * r + j * kCols / kGroup;
       if constexpr (F == kWMX) {
         const float X = e8m0_f32(blk[kCodeBytes + gi]);
-        if (w_bf16) {
-          ob = mx8_bf16(codes, X);
+        if constexpr (BF16) {
+          *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(W) + n * K + k) = mx8_bf16(codes, X);
         } else {
           const f32x2 a = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(codes, X, 0);
           const f32x2 c = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(codes, X, 1);
-          const f32x2 e = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(codes, X, 2);
-          const f32x2 g = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(codes, X, 3);
-          of[0] = a[0]; of[1] = a[1]; of[2] = c[0]; of[3] = c[1];
-          of[4] = e[0]; of[5] = e[1]; of[6] = g[0]; of[7] = g[1];
+          *reinterpret_cast<f32x4*>(static_cast<float*>(W) + n * K + k) = (f32x4){a[0], a[1], c[0], c[1]};
         }
       } else {
         const float d512 = bf16_to_f32(*reinterpret_cast<const uint16_t*>(blk + kCodeBytes + 2 * gi)) * 512.0f;
         const float m = bf16_to_f32(*reinterpret_cast<const uint16_t*>(blk + kCodeBytes + kScaleBytes + 2 * gi));
-        if (w_bf16) {
-          ob = dequant8_bf16(codes, d512, m);
+        if constexpr (BF16) {
+          *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(W) + n * K + k) = dequant8_bf16(codes, d512, m);
         } else {
-          const uint32_t lo = opaque(codes & 0x0F0F0F0Fu);          // columns 0, 2, 4, 6
-          const uint32_t hi = opaque((codes >> 4) & 0x0F0F0F0Fu);   // columns 1, 3, 5, 7
-          const f32x2 a = codes2_f32<false>(lo), c = codes2_f32<true>(lo);
-          const f32x2 e = codes2_f32<false>(hi), g = codes2_f32<true>(hi);
-          of[0] = eq3(a[0], d512, m); of[1] = eq3(e[0], d512, m);
-          of[2] = eq3(a[1], d512, m); of[3] = eq3(e[1], d512, m);
-          of[4] = eq3(c[0], d512, m); of[5] = eq3(g[0], d512, m);
-          of[6] = eq3(c[1], d512, m); of[7] = eq3(g[1], d512, m);
+          const f32x2 e = codes2_f32<false>(codes & 0x0F0Fu);         // columns 0, 2
+          const f32x2 o = codes2_f32<false>((codes >> 4) & 0x0F0Fu);  // columns 1, 3
+          *reinterpret_cast<f32x4*>(static_cast<float*>(W) + n * K + k) =
+              (f32x4){eq3(e[0], d512, m), eq3(o[0], d512, m), eq3(e[1], d512, m), eq3(o[1], d512, m)};
         }
-      }
-      if (w_bf16) {
-        *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(W) + n * K + k) = ob;
-      } else {
-        f32x4* out = reinterpret_cast<f32x4*>(static_cast<float*>(W) + n * K + k);
-        out[0] = (f32x4){of[0], of[1], of[2], of[3]};
-        out[1] = (f32x4){of[4], of[5], of[6], of[7]};
       }
     }
   }
@@ -427,58 +415,55 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float* __restrict__
   }
 }
 
-// q4nx_mx_quantize: float32 weights -> MXFP4-variant blob, with the lane
-// mapping of quantize_kernel.  Per group (OCP MX v1.0 conversion): inputs
-// taken into the domain as above; amax = max |w|; shared exponent
+// q4nx_mx_quantize: float32 weights -> MXFP4-variant blob, with the loads and
+// the lane mapping of quantize_kernel.  Per group (OCP MX v1.0 conversion):
+// inputs taken into the domain as above; amax = max |w|; shared exponent
 // e = floor(log2 amax) - 2 (2 = the largest FP4 exponent), clamped to
 // [-100, 100], 0 for an all-zero group; each element w / 2^e rounded to the
 // nearest FP4 magnitude -- the midpoints of {0, .5, 1, 1.5, 2, 3, 4, 6} go to
-// the even mantissa -- saturating at 6, with the sign of w.  w / 2^e is exact
-// (a power-of-two scaling; a result below 2^-126 only ever rounds to 0).
-// The group maximum and the sign are read from the bit patterns, so that
-// denormal inputs give the same exponent and sign whatever the denormal mode.
-__device__ __forceinline__ uint32_t fp4_code(float w, float inv_x) {
-  const float a = fabsf(w) * inv_x;
-  const uint32_t m = (uint32_t)(a > 0.25f) + (uint32_t)(a >= 0.75f) + (uint32_t)(a > 1.25f) +
-                     (uint32_t)(a >= 1.75f) + (uint32_t)(a > 2.5f) + (uint32_t)(a >= 3.5f) + (uint32_t)(a > 5.0f);
-  const uint32_t bits = __float_as_uint(w);
-  return m | ((bits >> 31) && (bits & 0x7FFFFFFFu) ? 8u : 0u);  // -0 keeps code 0
-}
-
+// the even mantissa -- saturating at 6, with the sign of w (-0 is code 0):
+// gfx950's conversion of two float32 values over a power of two.  The group
+// maximum is read from the bit patterns, so that denormal inputs give the same
+// exponent whatever the denormal mode.  Seven comparisons a weight against
+// the midpoints and a group per lane from memory: 21504 x 5376 in 106 us.
 __global__ __launch_bounds__(256) void mx_quantize_kernel(const float* __restrict__ W, int64_t N, int64_t K,
                                                           int64_t KB, int64_t nblocks, uint8_t* __restrict__ blob) {
+  __shared__ __attribute__((aligned(16))) uint8_t slots[4][kQuantSlotBytes];
   const int t = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r = 8 * t + (lane >> 3), c = lane & 7;
   for (int64_t b = blockIdx.x; b < nblocks; b += gridDim.x) {
     const int64_t i = b / KB, j = b - i * KB;
-    const int64_t n = i * kBlockRows + r;
-    const int64_t k0 = j * kBlockCols + kGroup * c;
     uint8_t* blk = blob + b * kMxBlockBytes;
     u32x4 codes = (u32x4){0u, 0u, 0u, 0u};
     uint32_t eb = kMxPadScale;  // padding: code 0 with scale 1
-    if (n < N && k0 < K) {
-      float w[32];
-      const f32x4* src = reinterpret_cast<const f32x4*>(W + n * K + k0);
-#pragma unroll
-      for (int v = 0; v < 8; ++v) {
-        const f32x4 x = src[v];
-        w[4 * v + 0] = x[0];
-        w[4 * v + 1] = x[1];
-        w[4 * v + 2] = x[2];
-        w[4 * v + 3] = x[3];
-      }
+    float w[32];
+    load_groups(W, N, K, i * kBlockRows + 8 * t, j * kBlockCols, lane, slots[t], w);
+    if (i * kBlockRows + r < N && j * kBlockCols + kGroup * c < K) {
       uint32_t amax = 0;  // bits of max |w|
 #pragma unroll
       for (int e = 0; e < 32; ++e) {
-        const float x = w[e] != w[e] ? 0.0f : (fabsf(w[e]) > kQuantClamp ? copysignf(kQuantClamp, w[e]) : w[e]);
-        w[e] = x;
-        amax = max(amax, __float_as_uint(x) & 0x7FFFFFFFu);
+        const uint32_t bits = __float_as_uint(w[e]), mag = bits & 0x7FFFFFFFu;
+        // NaN (and -0) -> +0
+        w[e] = mag - 1u < 0x7F800000u ? w[e] : 0.0f;
+        amax = max(amax, __float_as_uint(w[e]) & 0x7FFFFFFFu);
+      }
+      if (amax > __float_as_uint(kQuantClamp)) {
+#pragma unroll
+        for (int e = 0; e < 32; ++e) w[e] = fminf(fmaxf(w[e], -kQuantClamp), kQuantClamp);
+        amax = __float_as_uint(kQuantClamp);
       }
       const int ex = amax == 0 ? 0 : max(-100, min(100, (int)(amax >> 23) - 127 - 2));
       eb = (uint32_t)(ex + 127);
-      const float inv_x = __uint_as_float((uint32_t)(127 - ex) << 23);  // 2^-ex
+      const float X = e8m0_f32(eb);
 #pragma unroll
-      for (int e = 0; e < 32; ++e) codes[e >> 3] |= fp4_code(w[e], inv_x) << (4 * (e & 7));
+      for (int u = 0; u < 4; ++u) {
+        uint32_t q = 0;
+        q = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(q, w[8 * u + 0], w[8 * u + 1], X, 0);
+        q = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(q, w[8 * u + 2], w[8 * u + 3], X, 1);
+        q = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(q, w[8 * u + 4], w[8 * u + 5], X, 2);
+        q = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(q, w[8 * u + 6], w[8 * u + 7], X, 3);
+        codes[u] = q;
+      }
     }
     *reinterpret_cast<u32x4*>(blk + 1024 * t + 16 * lane) = codes;
     blk[kCodeBytes + 64 * t + lane] = (uint8_t)eb;
@@ -2574,8 +2559,8 @@ static q4nx_status gemm_entry(int64_t M, int64_t N, int64_t K, const uint16_t* d
     st = launch_ks_config<WF>(c.ks, M, N, K, d_X, d_W, d_Y, y_bf16, stream);
   } else if (c.two_phase) {
     const int64_t KB = ceil_div(K, kBlockCols), nblocks = ceil_div(N, kBlockRows) * KB;
-    hipLaunchKernelGGL(dequant_kernel<kWQ4NX>, dim3((unsigned)std::min<int64_t>(nblocks, int64_t(1) << 20)),
-                       dim3(256), 0, stream, static_cast<const uint8_t*>(d_W), N, K, KB, nblocks, d_work, 1);
+    hipLaunchKernelGGL((dequant_kernel<kWQ4NX, true>), dim3((unsigned)std::min<int64_t>(nblocks, int64_t(1) << 20)),
+                       dim3(256), 0, stream, static_cast<const uint8_t*>(d_W), N, K, KB, nblocks, d_work);
     for (int i = 0; i < c.count && st == Q4NX_OK; ++i)
       st = launch_region<kWBf16>(c.plan[i], N, K, d_X, d_work, d_Y, y_bf16, stream, part);
   } else {
@@ -2713,9 +2698,12 @@ static q4nx_status dequant_entry(const void* d_blob, int64_t N, int64_t K, void*
   const int64_t nblocks = ceil_div(N, kBlockRows) * KB;
   const int64_t grid = std::min<int64_t>(nblocks, int64_t(1) << 20);
   const uint8_t* blob = static_cast<const uint8_t*>(d_blob);
-  const int w_bf16 = (w_dtype == Q4NX_BF16);
-  hipLaunchKernelGGL(dequant_kernel<F>, dim3((unsigned)grid), dim3(256), 0, stream, blob, N, K, KB, nblocks, d_W,
-                     w_bf16);
+  if (w_dtype == Q4NX_BF16)
+    hipLaunchKernelGGL((dequant_kernel<F, true>), dim3((unsigned)grid), dim3(256), 0, stream, blob, N, K, KB, nblocks,
+                       d_W);
+  else
+    hipLaunchKernelGGL((dequant_kernel<F, false>), dim3((unsigned)grid), dim3(256), 0, stream, blob, N, K, KB,
+                       nblocks, d_W);
   return check_launch(fn);
 }
 
