@@ -1385,84 +1385,91 @@ __global__ __launch_bounds__(kWideThreads) void gemm256_kernel(const uint16_t* _
     }
 }
 
-// ---- 256 x 128 tile, one wave per SIMD ------------------------------------
-// The 256 x 256 kernel's scheme on half the columns: four waves in a 2 x 2
-// grid, each owning a 128 x 64 sub-tile (8 MFMA accumulators), so a 16-deep
-// K slice is 8 MFMAs against 6 fragment reads.  A K step is four blocks of 8
-// MFMA slots:
-//   slices 0-1  fragment reads of the next slice at slots 0-5; the next step's
-//               X rows written on odd slots (bf16 W: x0-x3, x4-x7; packed W:
-//               two per slice, between the dequantized W writes at slots 3
-//               and 7), its weight group dequantized a quarter of 8 columns
-//               per slot (packed W)
-//   slice 2     reads; the rest of the writes (bf16 W: w0-w3; packed W: x4-x7)
-//   barrier
-//   slice 3     reads of slice 0 of the next step
-// with each global load of step + 3 issued one slot after the write that
-// frees its register.  The MFMA chain of every output is the same as in the
-// other kernels, hence the same bits.  K must be a multiple of 64 (shapes
-// with a K tail take the general kernel).  Against the general kernel's
-// 256 x 128 tiles (16 or 8 waves, the compiler's schedule), measured on MI355X
-// with the same bits: Gemma3-4B o 41.6 -> 38.2 us (Q4NX weights), the 4B
-// gate/up remainder 50.2 -> 44.7 us and the 27B o remainder 72.4 -> 55.1 us
-// (bf16 weights), an MXFP4-variant 4B q/k/v product 54.9 -> 44.5 us.
-constexpr int kW128LdsBytes = 2 * (256 + 128) * kLdsStride * 2;  // two stages of X (256 rows) and W (128 rows)
-
-template <int WF>
-struct Wide128Regs {
-  u32x4 x[8];
-  u32x4 q;
-  uint32_t s, m;
+// ---- tiles of 64 TI x 64 TJ, one wave per SIMD ------------------------------
+// The 256 x 256 kernel's scheme for any tile of 64 TI x 64 TJ with K a
+// multiple of 64: four waves in a 2 x 2 grid, each owning a 32 TI x 32 TJ
+// sub-tile, and a K step of four slices of P = TI TJ MFMA slots with the other
+// work spread evenly over them: the TI + TJ fragment reads of the next slice,
+// the stage writes of the next step's X (and bf16 W) over the 3P slots before
+// the barrier, its weight groups dequantized piece by piece, and each global
+// load of step s + 1 + D one slot after the write that frees its registers (D
+// register sets: 2, or 4 where a step is short).  The MFMA chain of every
+// output is the same as in the other kernels, hence the same bits.
+// Why a family of tiles: a launch costs whole rounds of tiles, so the tile
+// that fills the CUs once decides most products of a few hundred rows.
+// Measured on MI355X against the tiles there were before (256 x 256,
+// 256 x 128, 128 x 128 and 128 x 64), us: 300 rows of Gemma3-27B gate/up 254 ->
+// 166 (320 x 192; MXFP4 weights 220 -> 147), 512 rows of 4B gate/up 73 -> 64
+// (256 x 192), 128 rows 41 -> 28 (128 x 128, a wave per SIMD instead of two
+// on the compiler's schedule), 512 rows of 4B q/k/v 37 -> 26 (64 x 128).  Tiles of 64 x 64, 128 x 64, 128 x 192
+// and 192 x 192 were never the best and are not built.
+template <int TI, int TJ, int WF>
+struct TileRegs {
+  u32x4 x[2 * TI];
+  u32x4 q[(TJ + 1) / 2];
+  uint32_t s[(TJ + 1) / 2], m[(TJ + 1) / 2];
 };
-template <>
-struct Wide128Regs<kWBf16> {
-  u32x4 x[8];
-  u32x4 w[4];
+template <int TI, int TJ>
+struct TileRegs<TI, TJ, kWBf16> {
+  u32x4 x[2 * TI];
+  u32x4 w[2 * TJ];
 };
 
-template <int WF>
-__global__ __launch_bounds__(kWideThreads) void gemm256x128_kernel(const uint16_t* __restrict__ X,
-                                                                   const uint8_t* __restrict__ wsrc,
-                                                                   void* __restrict__ Y, int M, int N, int K, int ldy,
-                                                                   int KB, int NS, int tiles_n, int y_bf16) {
-  constexpr int TI = 4, TJ = 2;
+template <int TI, int TJ>
+constexpr int tile_lds_bytes() {
+  return 2 * (64 * TI + 64 * TJ) * kLdsStride * 2;
+}
+
+template <int TI, int TJ, int D, int WF>
+__global__ __launch_bounds__(kWideThreads, (tile_lds_bytes<TI, TJ>() <= 80 * 1024 ? 2 : 1)) void gemm_tile_kernel(
+    const uint16_t* __restrict__ X, const uint8_t* __restrict__ wsrc, void* __restrict__ Y, int M, int N, int K,
+    int ldy, int KB, int NS, int tiles_n, int y_bf16) {
+  constexpr int BM = 64 * TI, BN = 64 * TJ, P = TI * TJ, S = 3 * P;  // MFMAs per slice; slots before the barrier
+  constexpr bool WQ4 = WF != kWBf16;
+  constexpr int kBB = wblock_bytes<WF>();
+  constexpr int kG = (TJ + 1) / 2;  // packed weight groups per thread and step
+  constexpr int kXW = 2 * TI, kWW = 2 * TJ;
   extern __shared__ __attribute__((aligned(16))) uint16_t gl[];
-  uint16_t* const xs0 = gl;                          // [2][256][72]
-  uint16_t* const ws0 = gl + 2 * 256 * kLdsStride;   // [2][128][72]
+  uint16_t* const xs0 = gl;                        // [2][BM][72]
+  uint16_t* const ws0 = gl + 2 * BM * kLdsStride;  // [2][BN][72]
 
   int bm, bn;
   gemm_tile_of(blockIdx.x, gridDim.x, tiles_n, bm, bn);
-  const int m0 = bm * 256, n0 = bn * 128;
+  const int m0 = bm * BM, n0 = bn * BN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
 
-  const int rows_x = min(256, M - m0);
+  const int rows_x = min(BM, M - m0);
   const __amdgpu_buffer_rsrc_t rsx = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(X + (size_t)m0 * K), (short)0, rows_x * K * 2, 0x00020000);
-  constexpr bool WQ4 = WF != kWBf16;
-  constexpr int kBB = wblock_bytes<WF>();
-  const int s0 = n0 >> 5, nst = min(4, NS - s0), rows_w = min(128, N - n0);
+  const int s0 = n0 >> 5, nst = min(2 * TJ, NS - s0), rows_w = min(BN, N - n0);
   const __amdgpu_buffer_rsrc_t rsw =
       WQ4 ? __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(wsrc + (size_t)s0 * KB * kBB), (short)0,
                                               nst * KB * kBB, 0x00020000)
           : __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(wsrc + (size_t)n0 * K * 2), (short)0,
                                               rows_w * K * 2, 0x00020000);
-  constexpr int kLoads = WF == kWQ4NX ? 11 : WF == kWMX ? 10 : 12;
 
-  const int c8 = tid & 7, half = tid & 1;
-  int vx[8];
+  const int c8 = tid & 7, hh = tid & 1;
+  int vx[kXW];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) vx[i] = (min((tid >> 3) + 32 * i, rows_x - 1) * K + 8 * c8) * 2;
-  int vq = 0, vs = 0, vw[4];
+  for (int i = 0; i < kXW; ++i) vx[i] = (min((tid >> 3) + 32 * i, rows_x - 1) * K + 8 * c8) * 2;
+  // Group g of a thread: row tid/2 + 128g of the tile, half tid%2 of the step.
+  // With an odd TJ the second half of the threads repeats the first half's
+  // last group (the same values to the same place).
+  int vq[kG], vs[kG], gr[kG], vw[kWW];
   if constexpr (WQ4) {
-    const int r = tid >> 1;
-    const int st = min(r >> 5, nst - 1), rr = r & 31;
-    vq = st * KB * kBB + 128 * rr + 16 * half;
-    vs = st * KB * kBB + kCodeBytes + (WF == kWMX ? 1 : 2) * (8 * rr + half);
+#pragma unroll
+    for (int g = 0; g < kG; ++g) {
+      const int row = (tid >> 1) + 128 * g;
+      gr[g] = row < BN ? row : row - 64;
+      const int st = min(gr[g] >> 5, nst - 1), rr = gr[g] & 31;
+      vq[g] = st * KB * kBB + 128 * rr + 16 * hh;
+      vs[g] = st * KB * kBB + kCodeBytes + (WF == kWMX ? 1 : 2) * (8 * rr + hh);
+    }
   } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) vw[i] = (min((tid >> 3) + 32 * i, rows_w - 1) * K + 8 * c8) * 2;
+    for (int i = 0; i < kWW; ++i) vw[i] = (min((tid >> 3) + 32 * i, rows_w - 1) * K + 8 * c8) * 2;
   }
   const int nsteps = K / kBK;
 
@@ -1474,166 +1481,149 @@ __global__ __launch_bounds__(kWideThreads) void gemm256x128_kernel(const uint16_
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.0f;
 
-  // Global load i of step t (clamped to the last step) into R.
-  auto load1 = [&](Wide128Regs<WF>& R, int t, int i) {
+  using Regs = TileRegs<TI, TJ, WF>;
+  auto load_x = [&](Regs& R, int t, int i) {
+    R.x[i] = __builtin_bit_cast(
+        u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsx, vx[i], 2 * kBK * min(t, nsteps - 1), 0));
+  };
+  auto load_w = [&](Regs& R, int t, int i) {
     const int k0 = min(t, nsteps - 1) * kBK;
-    const int sq = (k0 >> 8) * kBB + 16 * ((k0 & 255) >> 5);
-    const int ss = (k0 >> 8) * kBB + (WF == kWMX ? 1 : 2) * ((k0 & 255) >> 5);
-    if (i < 8) {
-      R.x[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsx, vx[i], 2 * k0, 0));
-      return;
-    }
     if constexpr (!WQ4) {
-      R.w[i - 8] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsw, vw[i - 8], 2 * k0, 0));
-    } else if (i == 8) {
-      R.q = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsw, vq + sq, 0, kNtLoad));
-    } else if (i == 9) {
-      if constexpr (WF == kWMX)
-        R.s = __builtin_amdgcn_raw_buffer_load_b8(rsw, vs + ss, 0, kNtLoad);
-      else
-        R.s = __builtin_amdgcn_raw_buffer_load_b16(rsw, vs + ss, 0, kNtLoad);
+      R.w[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsw, vw[i], 2 * k0, 0));
     } else {
-      R.m = __builtin_amdgcn_raw_buffer_load_b16(rsw, vs + ss + kScaleBytes, 0, kNtLoad);
+      const int c = (k0 & 255) >> 5, sb = (k0 >> 8) * kBB;
+      R.q[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsw, vq[i] + sb + 16 * c, 0, kNtLoad));
+      if constexpr (WF == kWMX) {
+        R.s[i] = __builtin_amdgcn_raw_buffer_load_b8(rsw, vs[i] + sb + c, 0, kNtLoad);
+      } else {
+        R.s[i] = __builtin_amdgcn_raw_buffer_load_b16(rsw, vs[i] + sb + 2 * c, 0, kNtLoad);
+        R.m[i] = __builtin_amdgcn_raw_buffer_load_b16(rsw, vs[i] + sb + 2 * c + kScaleBytes, 0, kNtLoad);
+      }
     }
   };
-  auto xs_row = [&](int st) { return xs0 + st * 256 * kLdsStride + (tid >> 3) * kLdsStride + 8 * c8; };
-  auto ws_row = [&](int st) { return ws0 + st * 128 * kLdsStride + (tid >> 1) * kLdsStride + kGroup * half; };
-  // Fragment i of K slice kq, in first-use order A0, B0, B1, A1, A2, A3.
-  const int fa = (128 * wm + (lane & 31)) * kLdsStride + 8 * (lane >> 5);
-  const int fb = (64 * wn + (lane & 31)) * kLdsStride + 8 * (lane >> 5);
+  auto write_x = [&](const Regs& R, int st, int k) {
+    *reinterpret_cast<u32x4*>(xs0 + st * BM * kLdsStride + ((tid >> 3) + 32 * k) * kLdsStride + 8 * c8) = R.x[k];
+  };
+  auto write_w = [&](const Regs& R, int st, int k) {
+    if constexpr (!WQ4)
+      *reinterpret_cast<u32x4*>(ws0 + st * BN * kLdsStride + ((tid >> 3) + 32 * k) * kLdsStride + 8 * c8) = R.w[k];
+  };
+  GroupDequant<WF> gdq;
+  auto wpiece = [&](const Regs& R, int st, int p) {
+    if constexpr (WQ4) {
+      const int g = p >> 4;
+      gdq.piece(R.q[g], R.s[g], WF == kWMX ? 0u : R.m[g], p & 15,
+                ws0 + st * BN * kLdsStride + gr[g] * kLdsStride + kGroup * hh);
+    }
+  };
+  const int fa = (32 * TI * wm + (lane & 31)) * kLdsStride + 8 * (lane >> 5);
+  const int fb = (32 * TJ * wn + (lane & 31)) * kLdsStride + 8 * (lane >> 5);
+  // Fragment i of K slice kq, in first-use order A0, B0 .. , A1 ..
   auto read1 = [&](int st, int kq, bf16x8 (&A)[TI], bf16x8 (&B)[TJ], int i) {
-    const uint16_t* xs = xs0 + st * 256 * kLdsStride + fa + 16 * kq;
-    const uint16_t* ws = ws0 + st * 128 * kLdsStride + fb + 16 * kq;
+    const uint16_t* xs = xs0 + st * BM * kLdsStride + fa + 16 * kq;
+    const uint16_t* ws = ws0 + st * BN * kLdsStride + fb + 16 * kq;
     if (i == 0) A[0] = *reinterpret_cast<const bf16x8*>(xs);
-    else if (i <= 2) B[i - 1] = *reinterpret_cast<const bf16x8*>(ws + 32 * (i - 1) * kLdsStride);
-    else A[i - 2] = *reinterpret_cast<const bf16x8*>(xs + 32 * (i - 2) * kLdsStride);
+    else if (i <= TJ) B[i - 1] = *reinterpret_cast<const bf16x8*>(ws + 32 * (i - 1) * kLdsStride);
+    else A[i - TJ] = *reinterpret_cast<const bf16x8*>(xs + 32 * (i - TJ) * kLdsStride);
   };
   auto mma1 = [&](const bf16x8 (&A)[TI], const bf16x8 (&B)[TJ], int i) {
-    acc[i >> 1][i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[i >> 1], B[i & 1], acc[i >> 1][i & 1], 0, 0, 0);
+    acc[i / TJ][i % TJ] =
+        __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[i / TJ], B[i % TJ], acc[i / TJ][i % TJ], 0, 0, 0);
   };
-  // The thread's weight group of the next step dequantized piece by piece.
-  GroupDequant<WF> gdq;
-  auto wpiece = [&](const Wide128Regs<WF>& R, int st, int p) {
-    if constexpr (WQ4) gdq.piece(R.q, R.s, WF == kWMX ? 0u : R.m, p, ws_row(st));
+  // Slots of the stage writes of step s + 1 among the S slots before the
+  // barrier, evenly spaced, and of the loads that reuse their registers, one
+  // slot later.
+  constexpr int kPieces = WQ4 ? 16 * kG : 0;
+  constexpr int kPSlots = kPieces <= 2 * P ? 2 * P : S;
+  constexpr int kWrites = kXW + (WQ4 ? 0 : kWW);
+  const auto wslot = [](int k) { return ((2 * k + 1) * S) / (2 * kWrites); };
+  const auto pslot = [](int p) { return (p * kPSlots) / (kPieces ? kPieces : 1); };
+  auto side = [&](Regs& Rs, int nxt, int s, int g) {
+    if constexpr (WQ4) {
+#pragma unroll
+      for (int p = 0; p < kPieces; ++p)
+        if (pslot(p) == g) wpiece(Rs, nxt, p);
+    }
+#pragma unroll
+    for (int k = 0; k < kWrites; ++k) {
+      if (wslot(k) == g) {
+        if (k < kXW) write_x(Rs, nxt, k);
+        else write_w(Rs, nxt, k - kXW);
+      }
+      if (wslot(k) + 1 == g) {
+        if (k < kXW) load_x(Rs, s + 1 + D, k);
+        else load_w(Rs, s + 1 + D, k - kXW);
+      }
+    }
+    if constexpr (WQ4) {
+#pragma unroll
+      for (int w = 0; w < kG; ++w)
+        if (pslot(16 * w + 15) + 1 == g) load_w(Rs, s + 1 + D, w);
+    }
   };
-  auto xwrite = [&](const Wide128Regs<WF>& R, uint16_t* xsn, int k) {
-    *reinterpret_cast<u32x4*>(xsn + 32 * k * kLdsStride) = R.x[k];
-  };
-  auto wwrite = [&](const Wide128Regs<WF>& R, int st, int k) {
-    if constexpr (!WQ4)
-      *reinterpret_cast<u32x4*>(xs0 + 2 * 256 * kLdsStride + st * 128 * kLdsStride +
-                                ((tid >> 3) + 32 * k) * kLdsStride + 8 * c8) = R.w[k];
-  };
-
   bf16x8 A0[TI], B0[TJ], A1[TI], B1[TJ];
-  // Work of slot i of slice sl besides the MFMA and the fragment read: the
-  // stage writes of step s+1 (from Rs) and the loads of step s+3 (into Rs).
-  auto side = [&](Wide128Regs<WF>& Rs, uint16_t* xsn, int nxt, int s, int sl, int i) {
-    if constexpr (!WQ4) {
-      // writes: slice 0 x0-x3, slice 1 x4-x7, slice 2 w0-w3 on odd slots;
-      // load k one slot after write k (slot 0 of the next slice after slot 7)
-      if (sl < 3 && (i & 1)) {
-        const int k = 4 * sl + (i >> 1);
-        if (k < 8) xwrite(Rs, xsn, k);
-        else wwrite(Rs, nxt, k - 8);
-      }
-      if (!(i & 1)) {
-        const int k = i == 0 ? 4 * sl - 1 : 4 * sl + (i >> 1) - 1;  // the write one slot back
-        if (k >= 0 && k < 12 && !(sl == 3 && i > 0)) load1(Rs, s + 3, k);
-      }
-    } else {
-      // dequant pieces 0-7 in slice 0, 8-15 in slice 1 (W writes at slots 3
-      // and 7); X writes: slice 0 slots 1, 5; slice 1 slots 1, 5; slice 2
-      // odd slots; loads: x one slot after its write, the scale (and offset)
-      // after piece 0 consumed them, the codes in slice 2 after piece 15.
-      if (sl < 2) wpiece(Rs, nxt, 8 * sl + i);
-      int kx = -1;
-      if (sl < 2 && (i == 1 || i == 5)) kx = 2 * sl + (i >> 2);
-      if (sl == 2 && (i & 1)) kx = 4 + (i >> 1);
-      if (kx >= 0) xwrite(Rs, xsn, kx);
-      int kl = -1;
-      if (sl < 2 && (i == 2 || i == 6)) kl = 2 * sl + (i >> 2);
-      if (sl == 2 && !(i & 1) && i > 0) kl = 4 + (i >> 1) - 1;
-      if (sl == 3 && i == 0) kl = 7;
-      if (kl >= 0) load1(Rs, s + 3, kl);
-      if (sl == 0 && i == 4) load1(Rs, s + 3, 9);                         // scale
-      if (WF == kWQ4NX && sl == 0 && i == 6) load1(Rs, s + 3, 10);        // offset
-      if (sl == 2 && i == 0) load1(Rs, s + 3, 8);                         // codes
+  auto slice = [&](int sl, const bf16x8 (&A)[TI], const bf16x8 (&B)[TJ], bf16x8 (&An)[TI], bf16x8 (&Bn)[TJ], int rst,
+                   int rkq, Regs& Rs, int nxt, int s) {
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      mma1(A, B, i);
+#pragma unroll
+      for (int f = 0; f < TI + TJ; ++f)
+        if (f * P / (TI + TJ) == i) read1(rst, rkq, An, Bn, f);
+      side(Rs, nxt, s, sl * P + i);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
-  auto step = [&](int s, Wide128Regs<WF>& Rs) {
-    const int cur = s & 1, nxt = cur ^ 1;
-    uint16_t* xsn = xs_row(nxt);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      mma1(A0, B0, i);
-      if (i < 6) read1(cur, 1, A1, B1, i);
-      side(Rs, xsn, nxt, s, 0, i);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      mma1(A1, B1, i);
-      if (i < 6) read1(cur, 2, A0, B0, i);
-      side(Rs, xsn, nxt, s, 1, i);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      mma1(A0, B0, i);
-      if (i < 6) read1(cur, 3, A1, B1, i);
-      side(Rs, xsn, nxt, s, 2, i);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+  auto step = [&](int s, int cur, Regs& Rs) {
+    const int nxt = cur ^ 1;
+    slice(0, A0, B0, A1, B1, cur, 1, Rs, nxt, s);
+    slice(1, A1, B1, A0, B0, cur, 2, Rs, nxt, s);
+    slice(2, A0, B0, A1, B1, cur, 3, Rs, nxt, s);
     __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      mma1(A1, B1, i);
-      if (i < 6) read1(nxt, 0, A0, B0, i);
-      side(Rs, xsn, nxt, s, 3, i);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    slice(3, A1, B1, A0, B0, nxt, 0, Rs, nxt, s);
   };
 
-  Wide128Regs<WF> R0, R1;
+  // Register set t % D holds the operands of step t; step 0 goes to LDS at once.
+  Regs R[D];
 #pragma unroll
-  for (int i = 0; i < kLoads; ++i) load1(R0, 0, i);
+  for (int t = 0; t < D; ++t) {
 #pragma unroll
-  for (int i = 0; i < kLoads; ++i) load1(R1, 1, i);
-  {
-    uint16_t* xs = xs_row(0);
+    for (int i = 0; i < kXW; ++i) load_x(R[t], t, i);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) xwrite(R0, xs, i);
-    if constexpr (WF == kWMX) {
-      const float Xs = e8m0_f32(R0.s);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) *reinterpret_cast<u32x4*>(ws_row(0) + 8 * u) = mx8_bf16(R0.q[u], Xs);
-    } else if constexpr (WQ4) {
-      const float d512 = bf16_to_f32(R0.s) * 512.0f, m = bf16_to_f32(R0.m);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) *reinterpret_cast<u32x4*>(ws_row(0) + 8 * u) = dequant8_bf16(R0.q[u], d512, m);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) wwrite(R0, 0, i);
-    }
+    for (int i = 0; i < (WQ4 ? kG : kWW); ++i) load_w(R[t], t, i);
   }
 #pragma unroll
-  for (int i = 0; i < kLoads; ++i) load1(R0, 2, i);
+  for (int i = 0; i < kXW; ++i) write_x(R[0], 0, i);
+  if constexpr (WQ4) {
+#pragma unroll
+    for (int p = 0; p < kPieces; ++p) wpiece(R[0], 0, p);
+  } else {
+#pragma unroll
+    for (int i = 0; i < kWW; ++i) write_w(R[0], 0, i);
+  }
+#pragma unroll
+  for (int i = 0; i < kXW; ++i) load_x(R[0], D, i);
+#pragma unroll
+  for (int i = 0; i < (WQ4 ? kG : kWW); ++i) load_w(R[0], D, i);
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < 6; ++i) read1(0, 0, A0, B0, i);
+  for (int i = 0; i < TI + TJ; ++i) read1(0, 0, A0, B0, i);
+  // D steps per trip, so the register sets stay static (D is even, so the
+  // stages do too).
   int s = 0;
-  for (; s + 1 < nsteps; s += 2) {
-    step(s, R1);
-    step(s + 1, R0);
+  for (; s + D <= nsteps; s += D) {
+#pragma unroll
+    for (int p = 0; p < D; ++p) step(s + p, p & 1, R[(p + 1) % D]);
   }
-  if (s < nsteps) step(s, R1);
+#pragma unroll
+  for (int p = 0; p < D - 1; ++p)
+    if (s + p < nsteps) step(s + p, p & 1, R[(p + 1) % D]);
 
-  const bool full = m0 + 256 <= M && n0 + 128 <= N;
+  const bool full = m0 + BM <= M && n0 + BN <= N;
   if (full && ldy < kFastStoreMaxLdy) {
     store_wave_tile(acc,
-                    static_cast<char*>(Y) + ((size_t)(unsigned)(m0 + 128 * wm) * (unsigned)ldy +
-                                             (unsigned)(n0 + 64 * wn)) * (y_bf16 ? 2u : 4u),
+                    static_cast<char*>(Y) + ((size_t)(unsigned)(m0 + 32 * TI * wm) * (unsigned)ldy +
+                                             (unsigned)(n0 + 32 * TJ * wn)) * (y_bf16 ? 2u : 4u),
                     ldy, y_bf16);
     return;
   }
@@ -1641,10 +1631,10 @@ __global__ __launch_bounds__(kWideThreads) void gemm256x128_kernel(const uint16_
   for (int a = 0; a < TI; ++a)
 #pragma unroll
     for (int b = 0; b < TJ; ++b) {
-      const int col = n0 + 64 * wn + 32 * b + (lane & 31);
+      const int col = n0 + 32 * TJ * wn + 32 * b + (lane & 31);
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const int row = m0 + 128 * wm + 32 * a + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+        const int row = m0 + 32 * TI * wm + 32 * a + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
         if (full || (row < M && col < N)) {
           if (y_bf16)
             static_cast<uint16_t*>(Y)[(size_t)row * ldy + col] = f32_to_bf16_bits(acc[a][b][e]);
@@ -1705,9 +1695,8 @@ __global__ __launch_bounds__(256) void splitk_sum_kernel(const float* __restrict
 }
 
 // ---- general tiles, two waves per SIMD --------------------------------------
-// Workgroup tile BM (tokens) x BN (outputs) for the shapes the 256 x 256 and
-// 256 x 128 hand-scheduled tiles do not serve (128 x 128 and 128 x 64 tiles,
-// 256 x 128 tiles with a K tail).  WAVES_M x WAVES_N waves; each owns a (BM/WAVES_M) x
+// Workgroup tile BM (tokens) x BN (outputs) for the K the hand-scheduled tiles
+// do not serve: not a multiple of 64, or past their range.  WAVES_M x WAVES_N waves; each owns a (BM/WAVES_M) x
 // (BN/WAVES_N) sub-tile.  LDS holds two stages of the X tile and of the
 // dequantized W tile; a K step runs the MFMAs of step k from one stage while
 // the same waves dequantize step k+1 into the other, with the raw global data
@@ -2170,12 +2159,10 @@ __global__ __launch_bounds__(64 * W, MT * NT >= 16 || MT > 4 ? 1 : 2) void gemm_
 }
 
 // ---- launch planning ----------------------------------------------------------
-// Tile shapes: 0 = 256 x 256 (gemm256_kernel; the general kernel past
-// kWideMaxK), 1 = 256 x 128 (gemm256x128_kernel; the general kernel with a K
-// tail or past kWideMaxK), 2 = 128 x 128, 3 = 128 x 64 (the general kernel).
-// The round costs below were measured with the general kernel's 256 x 128
-// tiles; the one-wave-per-SIMD form is faster on the Gemma3 shapes it serves,
-// which only favours the plans that use it.
+// Tile shapes of the plan: 0 = 256 x 256, 1 = 256 x 128, 2 = 128 x 128, 3 =
+// 128 x 64, as the general kernel (256 x 256: gemm256_kernel) computes them;
+// where K allows, gemm_tile_kernel takes a region over (see kPlanWide).  The
+// round costs below were measured with the general kernel.
 struct GemmTile {
   int bm, bn;
   float round_cost;  // time of one full round (a tile on every CU), relative to shape 0
@@ -2321,42 +2308,138 @@ static size_t plan_work_bytes(const GemmRegion* plan, int count) {
 constexpr double kDequantLaunchUs = 3.0, kDequantBytesPerUs = 5.5e6;
 constexpr double kFusedExtraWide = 0.20, kFusedExtraSmall = 0.14;
 
-// Tiles of gemm_ks_kernel (16 mt rows x 16 nt outputs, K over `waves` waves).
-// unit_us: time of one 128-column unit of one tile on a CU, fitted on MI355X
-// from launches of one tile per CU over K = 2048 .. 21504 (Q4NX weights); a
-// tile costs kKsTileUs more for its first loads and final sum, a launch
-// kKsLaunchUs.
+// ---- the launches of a product ------------------------------------------------
+// gemm_plan above decides how much workspace a product asks for and whether a
+// part of it is split along K; what runs is the cheapest of that plan, one or
+// two launches of gemm_tile_kernel, and one of gemm_ks_kernel, by the times
+// below.  They were fitted on MI355X to launches over K = 1152 .. 21504 and 40
+// to 640 tiles and predict those within about a tenth.  Which of the three runs
+// depends on M, N, K, the device and whether there is a workspace alone, so
+// the three weight operands always take the same sums; the tiles, which do not
+// change a bit, are chosen for the operand.
+
+// A full round of gemm_tile_kernel's tiles over K columns takes fixed_us +
+// slope K (slope_us: Q4NX weights dequantized in the K loop; bf16_us: the
+// other operands); with a part u of the CUs at work the slope falls by
+// `relief` (1 - u): the larger tiles are bound by what the whole chip shares.
+struct WideTile {
+  int ti, tj;
+  float fixed_us, slope_us, bf16_us, relief;
+};
+constexpr WideTile kWideTiles[] = {{1, 2, 4.5f, 0.0067f, 0.0060f, 0.15f}, {2, 2, 5.0f, 0.0091f, 0.0082f, 0.20f},
+                                   {3, 2, 6.4f, 0.0128f, 0.0113f, 0.25f}, {4, 2, 8.0f, 0.0152f, 0.0135f, 0.50f},
+                                   {2, 4, 8.0f, 0.0171f, 0.0148f, 0.50f}, {5, 2, 8.5f, 0.0185f, 0.0165f, 0.50f},
+                                   {4, 3, 9.0f, 0.0225f, 0.0182f, 0.50f}, {3, 4, 9.0f, 0.0240f, 0.0211f, 0.50f},
+                                   {5, 3, 10.0f, 0.0295f, 0.0237f, 0.50f}, {4, 4, 9.5f, 0.0265f, 0.0242f, 0.50f}};
+constexpr int kWideConfigs = (int)(sizeof(kWideTiles) / sizeof(kWideTiles[0]));
+constexpr int kWideSquare = kWideConfigs - 1;  // 256 x 256
+constexpr int kPlanWide[4] = {kWideSquare, 3, 1, 0};  // what computes a region of a plan, by its tile
+constexpr int64_t kSquareLongK = 4096;
+// K that gemm_tile_kernel takes: whole steps, and 320 rows of X below 2^31 bytes.
+static bool wide_ok(int64_t K) { return K % kBK == 0 && K < kWideMaxK / 2; }
+constexpr double kExtraLaunchUs = 2.0;
+
+static double wide_us(const WideTile& t, double tiles, double K, int cus, bool dequant) {
+  const double full = std::floor(tiles / cus), u = tiles / cus - full;
+  const double k_us = (dequant ? t.slope_us : t.bf16_us) * K;
+  double us = full * (t.fixed_us + k_us);
+  if (u > 0.0) us += t.fixed_us + k_us * (1.0 - t.relief * (1.0 - u));
+  return us;
+}
+
+// Tiles of gemm_ks_kernel (16 mt rows x 16 nt outputs, K over `waves` waves):
+// a tile takes fixed_us + unit_us per 128-column unit on a CU, a launch
+// kKsLaunchUs more.
 struct KsTile {
   int mt, nt, waves;
-  float unit_us;
+  float fixed_us, unit_us;
 };
-constexpr KsTile kKsTiles[] = {{1, 1, 8, 0.09f}, {1, 2, 4, 0.15f}, {2, 2, 4, 0.17f}, {3, 2, 4, 0.25f},
-                               {2, 4, 4, 0.31f}, {3, 4, 4, 0.47f}, {4, 4, 4, 0.58f}, {5, 4, 4, 0.60f},
-                               {6, 4, 4, 0.72f}, {8, 4, 4, 0.85f}};
+constexpr KsTile kKsTiles[] = {{1, 1, 8, 1.0f, 0.09f}, {1, 2, 4, 1.0f, 0.15f}, {2, 2, 4, 0.9f, 0.18f}, {3, 2, 4, 1.6f, 0.23f},
+                               {2, 4, 4, 1.8f, 0.31f}, {3, 4, 4, 3.4f, 0.36f}, {4, 4, 4, 4.4f, 0.40f}, {5, 4, 4, 4.8f, 0.50f},
+                               {6, 4, 4, 5.1f, 0.57f}, {8, 4, 4, 6.6f, 0.675f}};
 constexpr int kKsConfigs = (int)(sizeof(kKsTiles) / sizeof(kKsTiles[0]));
-constexpr double kKsLaunchUs = 3.2, kKsTileUs = 1.2;
+constexpr double kKsLaunchUs = 3.2;
 constexpr int64_t kKsMaxTiles = 16384;  // beyond it the chip is full many times over
-// What a full round of the other kernels' tiles takes, for the comparison:
-// round_us below overestimates small launches, whose plans it only ranks.
-// Measured on MI355X at K = 1152 .. 21504.
-constexpr double kTileFixedUs = 16.0, kTilePerKUs = 0.0237;
-constexpr double kTileCost[4] = {0.88, 0.55, 0.50, 0.38};
 
-// Index of the gemm_ks_kernel tile to use for a product that the plan would
-// otherwise compute, or -1 where the plan is estimated to be faster.  Only M,
-// N, K, the device and whether there is a workspace count, so the three
-// weight operands always take the same sums.
-static int ks_choose(int64_t M, int64_t N, int64_t K, int cus, const GemmRegion* plan, int count) {
-  if (K >= kWideMaxK) return -1;
-  double best = 0.0;
-  for (int i = 0; i < count; ++i) {
-    const GemmTile& t = kGemmTiles[plan[i].tile];
-    const double tiles = (double)ceil_div(plan[i].M, t.bm) * (double)ceil_div(plan[i].N, t.bn) * plan[i].ks;
-    const double k = (double)K / plan[i].ks;
-    best += std::ceil(tiles / cus) * kTileCost[plan[i].tile] * (kTileFixedUs + kTilePerKUs * k);
-    if (plan[i].ks > 1)
-      best += kSumLaunchUs + (4.0 * plan[i].ks + 4.0) * (double)plan[i].M * (double)plan[i].N / kSumBytesPerUs;
+// What a full round of the plan's tiles (kGemmTiles) takes: those the general
+// kernel still computes (K with a tail, or past the wide kernels' range) and
+// 256 x 256 ones.  (round_us overestimates small launches; it only ranks the
+// plan's own choices.)
+constexpr double kTileFixedUs = 16.0, kTilePerKUs = 0.0237;
+constexpr double kTileCost[4] = {0.88, 0.65, 0.50, 0.38};
+
+struct WideRegion {
+  int tile;  // of kWideTiles
+  int64_t m0, n0, M, N;
+};
+
+// One launch of gemm_tile_kernel, or two over a split of the rows or columns
+// (whole rounds of a large tile, then the rest), and their estimated time.
+static int wide_plan(int64_t M, int64_t N, int64_t K, int cus, bool dequant, WideRegion (&plan)[2], double* est_us) {
+  const auto tiles = [](const WideTile& t, int64_t m, int64_t n) {
+    return (double)ceil_div(m, 64 * t.ti) * (double)ceil_div(n, 64 * t.tj);
+  };
+  double best = 1e300;
+  int count = 0;
+  for (int a = 0; a < kWideConfigs; ++a) {
+    const double c = wide_us(kWideTiles[a], tiles(kWideTiles[a], M, N), (double)K, cus, dequant);
+    if (c < best) {
+      best = c;
+      plan[0] = {a, 0, 0, M, N};
+      count = 1;
+    }
   }
+  for (int a : {kWideSquare, 6, 3}) {  // 256 x 256, 256 x 192, 256 x 128
+    const WideTile& t = kWideTiles[a];
+    const int64_t tm = ceil_div(M, 64 * t.ti), tn = ceil_div(N, 64 * t.tj), full = tm * tn / cus;
+    if (full < 1) continue;
+    for (int dir = 0; dir < 2; ++dir) {
+      // Largest leading block of rows (dir 0) or columns (dir 1) whose tiles
+      // fit in the whole rounds.
+      const int64_t split = dir == 0 ? (full * cus / tn) * 64 * t.ti : (full * cus / tm) * 64 * t.tj;
+      if (split <= 0 || split >= (dir == 0 ? M : N)) continue;
+      const int64_t ma = dir == 0 ? split : M, na = dir == 0 ? N : split;
+      const int64_t mb = dir == 0 ? M - split : M, nb = dir == 0 ? N : N - split;
+      const double ca = wide_us(t, tiles(t, ma, na), (double)K, cus, dequant) + kExtraLaunchUs;
+      for (int b = 0; b < kWideConfigs; ++b) {
+        const double c = ca + wide_us(kWideTiles[b], tiles(kWideTiles[b], mb, nb), (double)K, cus, dequant);
+        if (c < best) {
+          best = c;
+          plan[0] = {a, 0, 0, ma, na};
+          plan[1] = {b, dir == 0 ? split : 0, dir == 0 ? 0 : split, mb, nb};
+          count = 2;
+        }
+      }
+    }
+  }
+  *est_us = best;
+  return count;
+}
+
+static double plan_us(const GemmRegion* plan, int count, int64_t K, int cus) {
+  double us = 0.0;
+  for (int i = 0; i < count; ++i) {
+    const GemmRegion& r = plan[i];
+    const GemmTile& t = kGemmTiles[r.tile];
+    const double tiles = (double)ceil_div(r.M, t.bm) * (double)ceil_div(r.N, t.bn) * r.ks;
+    if (r.ks == 1 && wide_ok(K)) {
+      const WideTile& w = kWideTiles[kPlanWide[r.tile]];
+      us += wide_us(w, (double)ceil_div(r.M, 64 * w.ti) * (double)ceil_div(r.N, 64 * w.tj), (double)K, cus, true);
+    } else if (wide_ok(K)) {
+      us += wide_us(kWideTiles[kWideSquare], tiles, (double)K / r.ks, cus, true);
+    } else {
+      us += std::ceil(tiles / cus) * kTileCost[r.tile] * (kTileFixedUs + kTilePerKUs * (double)K / r.ks);
+    }
+    if (r.ks > 1)
+      us += kSumLaunchUs + (4.0 * r.ks + 4.0) * (double)r.M * (double)r.N / kSumBytesPerUs;
+    if (i > 0) us += kExtraLaunchUs;
+  }
+  return us;
+}
+
+// The fastest gemm_ks_kernel tile for a product that takes `best` us
+// otherwise, or -1 if none is faster.
+static int ks_choose(int64_t M, int64_t N, int64_t K, int cus, double best) {
   int pick = -1;
   const double units = (double)ceil_div(K, kKsUnit);
   for (int i = 0; i < kKsConfigs; ++i) {
@@ -2366,7 +2449,7 @@ static int ks_choose(int64_t M, int64_t N, int64_t K, int cus, const GemmRegion*
     // Small tiles share a CU, so a part of a round costs its share.
     double load = std::max(1.0, (double)tiles / cus);
     if (t.mt * t.nt >= 16) load = std::ceil(load);
-    const double c = kKsLaunchUs + load * (kKsTileUs + units * t.unit_us);
+    const double c = kKsLaunchUs + load * (t.fixed_us + units * t.unit_us);
     if (c < best) {
       best = c;
       pick = i;
@@ -2378,21 +2461,21 @@ static int ks_choose(int64_t M, int64_t N, int64_t K, int cus, const GemmRegion*
 struct GemmChoice {
   GemmRegion plan[2];
   int count;
-  int ks;             // index into kKsTiles: one launch of gemm_ks_kernel instead of the plan; -1: the plan
+  WideRegion wide[2];
+  int wide_count;     // launches of gemm_tile_kernel instead of the plan (0: the plan)
+  int ks;             // index into kKsTiles: one launch of gemm_ks_kernel instead of either; -1: not
   bool two_phase;
   size_t w_bytes;     // bf16 W at the start of the workspace (two-phase only)
   size_t part_bytes;  // split-K partial products after it
 };
 
-// (The workspace a call asks for is that of the plan, also where gemm_ks_kernel
-// takes the product and leaves it unused: callers size and keep workspaces by
-// it.)
+// (The workspace a call asks for is that of the plan, also where other
+// launches leave it unused: callers size and keep workspaces by it.)
 static GemmChoice gemm_choose(int wf, int64_t M, int64_t N, int64_t K, bool have_work) {
   GemmChoice c{};
   double est_us = 0.0;
   const int cus = device_cus();
   c.count = gemm_plan(M, N, K, cus, have_work, c.plan, &est_us);
-  c.ks = ks_choose(M, N, K, cus, c.plan, c.count);
   c.part_bytes = plan_work_bytes(c.plan, c.count);
   const double deq_us = kDequantLaunchUs + (kBlockBytes / (double)(kBlockRows * kBlockCols) + 2.0) * (double)N *
                                                (double)K / kDequantBytesPerUs;
@@ -2400,6 +2483,17 @@ static GemmChoice gemm_choose(int wf, int64_t M, int64_t N, int64_t K, bool have
   const double extra = c.plan[0].tile == 0 ? kFusedExtraWide : kFusedExtraSmall;
   c.two_phase = have_work && wf == kWQ4NX && deq_us < extra * kloop_us;
   c.w_bytes = c.two_phase ? (size_t)ceil_div(N * K * 2, 256) * 256 : 0;
+  double best = plan_us(c.plan, c.count, K, cus), wide = 0.0;
+  if (wide_ok(K)) {
+    const int n = wide_plan(M, N, K, cus, true, c.wide, &wide);
+    if (wide <= best) {
+      best = wide;
+      c.wide_count = n;
+    }
+  }
+  c.ks = K < kWideMaxK ? ks_choose(M, N, K, cus, best) : -1;
+  if (c.ks < 0 && c.wide_count > 0 && (wf != kWQ4NX || c.two_phase))
+    c.wide_count = wide_plan(M, N, K, cus, false, c.wide, &wide);
   return c;
 }
 
@@ -2435,18 +2529,55 @@ static q4nx_status launch_gemm256(int64_t M, int64_t N, int64_t K, const uint16_
   return Q4NX_OK;
 }
 
-template <int WF>
-static q4nx_status launch_gemm256x128(int64_t M, int64_t N, int64_t K, const uint16_t* X, const void* blob, void* Y,
-                                      int64_t ldy, int y_bf16, hipStream_t stream) {
-  auto kern = gemm256x128_kernel<WF>;
+template <int TI, int TJ, int WF>
+static q4nx_status launch_tile(int64_t M, int64_t N, int64_t K, const uint16_t* X, const void* w, void* Y, int64_t ldy,
+                               int y_bf16, hipStream_t stream) {
+  constexpr int D = TI * TJ <= 2 ? 4 : 2;
+  auto kern = gemm_tile_kernel<TI, TJ, D, WF>;
+  constexpr int lds = tile_lds_bytes<TI, TJ>();
   static LdsReservation lds_res;
-  if (!lds_res.ensure(reinterpret_cast<const void*>(kern), kW128LdsBytes))
+  if (!lds_res.ensure(reinterpret_cast<const void*>(kern), lds))
     return fail(Q4NX_ERR_HIP, "q4nx_gemm: cannot reserve LDS");
-  const int64_t tiles_n = ceil_div(N, 128), tiles_m = ceil_div(M, 256);
-  hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_n * tiles_m)), dim3(kWideThreads), kW128LdsBytes, stream, X,
-                     static_cast<const uint8_t*>(blob), Y, (int)M, (int)N, (int)K, (int)ldy,
+  const int64_t tiles_n = ceil_div(N, 64 * TJ), tiles_m = ceil_div(M, 64 * TI);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_n * tiles_m)), dim3(kWideThreads), lds, stream, X,
+                     static_cast<const uint8_t*>(w), Y, (int)M, (int)N, (int)K, (int)ldy,
                      (int)ceil_div(K, kBlockCols), (int)ceil_div(N, kBlockRows), (int)tiles_n, y_bf16);
   return Q4NX_OK;
+}
+
+// X rows m0.., W rows n0.. (strips n0/32.. of a packed matrix) and Y at
+// (m0, n0) of a region of the product, in the given weight format.
+template <int WF>
+static void region_operands(int64_t m0, int64_t n0, int64_t N, int64_t K, int y_bf16, const uint16_t*& X,
+                            const void*& w, void*& Y) {
+  X += m0 * K;
+  w = static_cast<const uint8_t*>(w) +
+      (WF != kWBf16 ? (n0 / kBlockRows) * ceil_div(K, kBlockCols) * wblock_bytes<WF>() : 2 * n0 * K);
+  Y = static_cast<uint8_t*>(Y) + (m0 * N + n0) * (y_bf16 ? 2 : 4);
+}
+
+template <int WF>
+static q4nx_status launch_wide(const WideRegion& r, int64_t N, int64_t K, const uint16_t* X, const void* w, void* Y,
+                               int y_bf16, hipStream_t stream) {
+  region_operands<WF>(r.m0, r.n0, N, K, y_bf16, X, w, Y);
+  switch (r.tile) {
+    case 0: return launch_tile<1, 2, WF>(r.M, r.N, K, X, w, Y, N, y_bf16, stream);
+    case 1: return launch_tile<2, 2, WF>(r.M, r.N, K, X, w, Y, N, y_bf16, stream);
+    case 2: return launch_tile<3, 2, WF>(r.M, r.N, K, X, w, Y, N, y_bf16, stream);
+    case 3: return launch_tile<4, 2, WF>(r.M, r.N, K, X, w, Y, N, y_bf16, stream);
+    case 4: return launch_tile<2, 4, WF>(r.M, r.N, K, X, w, Y, N, y_bf16, stream);
+    case 5: return launch_tile<5, 2, WF>(r.M, r.N, K, X, w, Y, N, y_bf16, stream);
+    case 6: return launch_tile<4, 3, WF>(r.M, r.N, K, X, w, Y, N, y_bf16, stream);
+    case 7: return launch_tile<3, 4, WF>(r.M, r.N, K, X, w, Y, N, y_bf16, stream);
+    case 8: return launch_tile<5, 3, WF>(r.M, r.N, K, X, w, Y, N, y_bf16, stream);
+    default:
+      // Over a long K gemm256_kernel's own placement of the same work is ahead
+      // (bf16 weights, 27B gate/up's 160 x 16 tiles at K = 5376: 1427 against
+      // 1486 us), over a short one the even spacing (1B gate/up at 1024 rows,
+      // K = 1152: 44.1 against 40.9 us; level at K = 2560).
+      if (K >= kSquareLongK) return launch_gemm256<false, WF>(r.M, r.N, K, X, w, Y, N, y_bf16, stream);
+      return launch_tile<4, 4, WF>(r.M, r.N, K, X, w, Y, N, y_bf16, stream);
+  }
 }
 
 template <int MT, int NT, int W, int WF>
@@ -2486,18 +2617,13 @@ static q4nx_status launch_ks_config(int cfg, int64_t M, int64_t N, int64_t K, co
   }
 }
 
-// One region of the output: X rows m0.., W rows n0.. (strips n0/32.. of a
-// packed matrix) and Y at (m0, n0) with row stride N, so each launch sees an
-// ordinary smaller problem.
+// One region of a plan, an ordinary smaller problem.
 template <int WF>
-static q4nx_status launch_region(const GemmRegion& r, int64_t N, int64_t K, const uint16_t* X, const void* w,
-                                 void* Y, int y_bf16, hipStream_t stream, float* work) {
-  const uint16_t* Xr = X + r.m0 * K;
-  const void* Wr = WF != kWBf16
-                       ? static_cast<const void*>(static_cast<const uint8_t*>(w) +
-                                                  (r.n0 / kBlockRows) * ceil_div(K, kBlockCols) * wblock_bytes<WF>())
-                       : static_cast<const void*>(static_cast<const uint16_t*>(w) + r.n0 * K);
-  void* Yr = static_cast<uint8_t*>(Y) + (r.m0 * N + r.n0) * (y_bf16 ? 2 : 4);
+static q4nx_status launch_region(const GemmRegion& r, int64_t N, int64_t K, const uint16_t* Xr, const void* Wr,
+                                 void* Yr, int y_bf16, hipStream_t stream, float* work) {
+  if (r.ks == 1 && wide_ok(K))
+    return launch_wide<WF>({kPlanWide[r.tile], r.m0, r.n0, r.M, r.N}, N, K, Xr, Wr, Yr, y_bf16, stream);
+  region_operands<WF>(r.m0, r.n0, N, K, y_bf16, Xr, Wr, Yr);
   if (r.ks > 1) {
     // Partials [ks][r.M][r.N] in the workspace, then their sum into Y.
     const q4nx_status st = K % kBK != 0
@@ -2513,21 +2639,32 @@ static q4nx_status launch_region(const GemmRegion& r, int64_t N, int64_t K, cons
   switch (r.tile) {
     case 0:
       if (K >= kWideMaxK) return launch_gemm<256, 256, 2, 4, WF>(r.M, r.N, K, Xr, Wr, Yr, N, y_bf16, stream);
-      if (K % kBK != 0) return launch_gemm256<true, WF>(r.M, r.N, K, Xr, Wr, Yr, N, y_bf16, stream);
-      return launch_gemm256<false, WF>(r.M, r.N, K, Xr, Wr, Yr, N, y_bf16, stream);
+      return launch_gemm256<true, WF>(r.M, r.N, K, Xr, Wr, Yr, N, y_bf16, stream);
     case 1:
-      if (K % kBK == 0 && K < kWideMaxK) return launch_gemm256x128<WF>(r.M, r.N, K, Xr, Wr, Yr, N, y_bf16, stream);
-      // A K tail: the general kernel.  Q4NX weights as 16 waves of 32 x 64
-      // (four per SIMD), which hide the dequantization in the tile loads
-      // better than 8 waves of 64 x 64 (measured on MI355X: Gemma3 4B q/k/v
-      // 56.8 -> 55.5 us, o 42.2 -> 39.2 us with K a multiple of 64); bf16 and
-      // MXFP4-variant weights keep 8 waves (the 4B bf16 gate/up remainder ran
-      // 2.6% slower with 16).  Same MFMA chains, same bits.
+      // Q4NX weights as 16 waves of 32 x 64 (four per SIMD), which hide the
+      // dequantization in the tile loads better than 8 waves of 64 x 64
+      // (measured on MI355X: Gemma3 4B q/k/v 56.8 -> 55.5 us, o 42.2 -> 39.2 us
+      // with K a multiple of 64); bf16 and MXFP4-variant weights keep 8 waves
+      // (the 4B bf16 gate/up remainder ran 2.6% slower with 16).  Same MFMA
+      // chains, same bits.
       if constexpr (WF == kWQ4NX) return launch_gemm<256, 128, 8, 2, WF>(r.M, r.N, K, Xr, Wr, Yr, N, y_bf16, stream);
       else return launch_gemm<256, 128, 4, 2, WF>(r.M, r.N, K, Xr, Wr, Yr, N, y_bf16, stream);
     case 2: return launch_gemm<128, 128, 2, 4, WF>(r.M, r.N, K, Xr, Wr, Yr, N, y_bf16, stream);
     default: return launch_gemm<128, 64, 2, 2, WF>(r.M, r.N, K, Xr, Wr, Yr, N, y_bf16, stream);
   }
+}
+
+// The launches of gemm_tile_kernel, or the plan's.
+template <int WF>
+static q4nx_status launch_planned(const GemmChoice& c, int64_t N, int64_t K, const uint16_t* X, const void* w, void* Y,
+                                  int y_bf16, hipStream_t stream, float* part) {
+  q4nx_status st = Q4NX_OK;
+  for (int i = 0; i < c.wide_count && st == Q4NX_OK; ++i)
+    st = launch_wide<WF>(c.wide[i], N, K, X, w, Y, y_bf16, stream);
+  if (c.wide_count == 0)
+    for (int i = 0; i < c.count && st == Q4NX_OK; ++i)
+      st = launch_region<WF>(c.plan[i], N, K, X, w, Y, y_bf16, stream, part);
+  return st;
 }
 
 static q4nx_status check_launch(const char* fn);
@@ -2561,11 +2698,9 @@ static q4nx_status gemm_entry(int64_t M, int64_t N, int64_t K, const uint16_t* d
     const int64_t KB = ceil_div(K, kBlockCols), nblocks = ceil_div(N, kBlockRows) * KB;
     hipLaunchKernelGGL((dequant_kernel<kWQ4NX, true>), dim3((unsigned)std::min<int64_t>(nblocks, int64_t(1) << 20)),
                        dim3(256), 0, stream, static_cast<const uint8_t*>(d_W), N, K, KB, nblocks, d_work);
-    for (int i = 0; i < c.count && st == Q4NX_OK; ++i)
-      st = launch_region<kWBf16>(c.plan[i], N, K, d_X, d_work, d_Y, y_bf16, stream, part);
+    st = launch_planned<kWBf16>(c, N, K, d_X, d_work, d_Y, y_bf16, stream, part);
   } else {
-    for (int i = 0; i < c.count && st == Q4NX_OK; ++i)
-      st = launch_region<WF>(c.plan[i], N, K, d_X, d_W, d_Y, y_bf16, stream, part);
+    st = launch_planned<WF>(c, N, K, d_X, d_W, d_Y, y_bf16, stream, part);
   }
   if (st != Q4NX_OK) return st;
   return check_launch(fn);

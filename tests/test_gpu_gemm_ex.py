@@ -320,3 +320,48 @@ def test_gemm_few_rows(q4, M, N, K):
     q4.q4nx_gemm_bf16(M, N, K, X, W, Y[1])
     torch.cuda.synchronize()
     assert torch.equal(Y[0].view(torch.int32), Y[1].view(torch.int32))
+
+
+# One shape per tile of the hand-scheduled kernel (and two launches over a
+# split of the rows or the columns), as q4nx_gemm chooses them on a 256-CU
+# device for Q4NX weights: ragged M and N throughout, K of one, two, three and
+# five steps.  (Other weights may take other tiles; every tile sums in the
+# same order.)
+TILE_SHAPES = [(80, 5000, 64), (80, 20001, 64), (140, 20001, 64), (200, 20001, 64), (60, 43001, 64),
+               (260, 30001, 64), (400, 20001, 128), (140, 43001, 64), (260, 43001, 192), (580, 20001, 320),
+               (520, 30001, 64), (580, 30001, 64), (400, 43001, 192), (1999, 20001, 192)]
+
+
+@pytest.mark.parametrize("M,N,K", TILE_SHAPES)
+def test_gemm_tiles(q4, M, N, K):
+    """Sampled rows against the float64 product of the bf16 weights within the
+    tight bound, every element (packed, MXFP4 and bf16 weights, float32 and
+    bf16 outputs) against the same bits, nothing written past M x N."""
+    _say("gemm tiles", M, N, K)
+    codes, s, o = gen_weights(N, K, seed=M + N)
+    blob = dev_u8(q4.q4nx_pack(codes, s, o))
+    Xh = gen_activations((M, K), seed=K + M)
+    X = dev_bf16(Xh)
+    W = torch.empty((N, K), dtype=torch.bfloat16, device="cuda")
+    Y = [torch.full((M * N + 64,), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2)]
+    Yb = torch.full((M * N + 64,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    q4.q4nx_gemm(M, N, K, X, blob, Y[0])
+    q4.q4nx_dequant(blob, N, K, W)
+    q4.q4nx_gemm_bf16(M, N, K, X, W, Y[1])
+    q4.q4nx_gemm(M, N, K, X, blob, Yb)
+    torch.cuda.synchronize()
+    assert torch.equal(Y[0].view(torch.int32), Y[1].view(torch.int32))
+    assert torch.equal(Yb[:M * N].view(torch.int16), Y[0][:M * N].bfloat16().view(torch.int16))
+    assert torch.isnan(Y[0][M * N:]).all() and torch.isnan(Yb[M * N:]).all()
+    rng = np.random.default_rng(M)
+    rows = np.unique(np.concatenate([np.arange(4), M - 1 - np.arange(8), rng.integers(0, M, 8)]))
+    w16 = oracle.bf16_to_f32(oracle.f32_to_bf16(oracle.dequant_f32(codes, s, o)))
+    got = Y[0][:M * N].view(M, N)[torch.from_numpy(rows).cuda()].cpu().numpy().astype(np.float64)
+    assert (np.abs(got - oracle.gemm_f64(Xh[rows], w16)) <= 1e-5 * oracle.abs_bound(Xh[rows], w16) + 1e-6).all()
+    mcodes, msc = gen_mx_weights(N, K, seed=K, mode="edge")
+    mblob = dev_u8(q4.q4nx_mx_pack(mcodes, msc))
+    q4.q4nx_mx_gemm(M, N, K, X, mblob, Y[0])
+    q4.q4nx_mx_dequant(mblob, N, K, W)
+    q4.q4nx_gemm_bf16(M, N, K, X, W, Y[1])
+    torch.cuda.synchronize()
+    assert torch.equal(Y[0].view(torch.int32), Y[1].view(torch.int32))
