@@ -407,3 +407,13 @@ def test_flowkv_static_validates_before_hip():
     assert call(win=-1) == q4.Q4NX_ERR_SHAPE
     assert call(v=MIS) == q4.Q4NX_ERR_ALIGNMENT
     assert "q4nx_flowkv_decode_static" in L.q4nx_last_error().decode()
+
+
+def test_binding_blob_sizes_match_the_library():
+    """The binding's own blob sizes (its check before a device call) against
+    q4nx_packed_size and q4nx_mx_packed_size, invalid shapes included."""
+    big = 1 << 30
+    for N in (-1, 0, 1, 31, 32, 33, 5376, big, big + 1):
+        for K in (-32, 0, 31, 32, 80, 256, 288, 21504, big, big + 32):
+            assert q4._blob_bytes(N, K) == q4.q4nx_packed_size(N, K), (N, K)
+            assert q4._mx_blob_bytes(N, K) == q4.q4nx_mx_packed_size(N, K), (N, K)
