@@ -4,7 +4,7 @@
 // its sliding-window variant.
 //
 // The sweep is split in two launches.  Phase 1 gives every (KV group, chunk of
-// 16, 32, 64, 128, 256 or 512 positions) to one workgroup, which computes for the H/G query heads
+// 16 to 512 positions) to one workgroup, which computes for the H/G query heads
 // of the group the chunk's own running state: the max score m_c (Eq. 7), the
 // denominator l_c = sum exp(s - m_c) (Eq. 8, 10) and the weighted values
 // Y_c = sum exp(s - m_c) v (Eq. 11), into the caller's workspace.  Phase 2
@@ -29,12 +29,22 @@ namespace q4nx {
 typedef __bf16 bf16x2f __attribute__((ext_vector_type(2)));
 
 constexpr int kMinChunk = 16;      // smallest chunk: sizes the workspace
-constexpr int kFkvThreads = 256;   // 4 waves
+constexpr int kSubBytes = 8192;    // K (and V) bytes a wave takes at a time
+constexpr int kFkvThreads = 256;   // merge workgroups
 constexpr int kMergeRegs = 8;      // chunks per slice the one-pass merge holds in registers
 
 // a.lo * b.lo + a.hi * b.hi + c for two bf16 pairs (exact products, float32 sum).
 __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c) {
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2f, a), __builtin_bit_cast(bf16x2f, b), c, false);
+}
+
+// K and V are read once per call: non-temporal.  (Default loads took 8% longer
+// over the 4B layer stack at 32K and 9% over the 27B one at 16K, and were at
+// most 2% ahead where a whole model's cache stays on the chip.)
+__device__ __forceinline__ uint4 load_stream(const uint4* p) {
+  typedef unsigned u4 __attribute__((ext_vector_type(4)));
+  const u4 v = __builtin_nontemporal_load(reinterpret_cast<const u4*>(p));
+  return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
 __device__ __forceinline__ float bf16lo(uint32_t v) { return __uint_as_float(v << 16); }
@@ -50,15 +60,6 @@ __device__ __forceinline__ float wave_max(float v) {
   v = fmaxf(v, xor_lane<2>(v));
   return fmaxf(v, xor_lane<1>(v));
 }
-__device__ __forceinline__ float wave_sum(float v) {
-  v += xor_lane<32>(v);
-  v += xor_lane<16>(v);
-  v += xor_lane<8>(v);
-  v += xor_lane<4>(v);
-  v += xor_lane<2>(v);
-  return v + xor_lane<1>(v);
-}
-
 // Sum over the lanes l ^ m for m = R, 2R, ..., 32 (R a power of two, 8 to
 // 32), in that order.
 template <int R>
@@ -68,204 +69,215 @@ __device__ __forceinline__ float sum_lanes_from(float v) {
   return v + xor_lane<32>(v);
 }
 
-// Phase 1.  grid (chunks, G); CH cache positions per workgroup, D = head
-// dimension, HG = query heads per group.  Partial of (head, chunk) at
+// Phase 1.  grid (chunks, G), W waves: workgroup (c, g) covers `chunk`
+// positions from j0 + c chunk, each wave a contiguous part of them, for the HG
+// query heads of group g.  Partial of (head, chunk) at
 // work[(head * nchunks + chunk) * (D + 4)]: m_c, l_c, -, -, Y_c[D].
-template <int CH, int D, int HG, bool PRE>
-__global__ __launch_bounds__(kFkvThreads) void flowkv_chunk_kernel(const uint16_t* __restrict__ q,
-                                                                  const uint16_t* __restrict__ K,
-                                                                  const uint16_t* __restrict__ V, int64_t L,
-                                                                  int j0, int j1, float scale,
-                                                                  float* __restrict__ work) {
+//
+// A wave walks its part in sub-chunks of SP = 4096 / D positions (8 KiB of K
+// and of V: eight 16-byte loads per lane each) with FlowKV's running state
+// (Eq. 7-11), no barrier and no workgroup-wide phase: K of the next sub-chunk
+// is requested as soon as the scores are out of its registers, V as soon as
+// the weighted sums are, so the wave always has loads in flight; the waves'
+// states are merged at the end, through LDS.  Short ranges (the sliding-window
+// layers) are bound by latency and take one wave and one sub-chunk per
+// workgroup: one round trip for q, K and V together, and none of the six
+// barriers of a workgroup that forms one softmax.  Measured on MI355X over the
+// Gemma3 layer stacks against such workgroups (us): 4B at 32K 386 -> 332, at
+// 1024 270 -> 224, 27B at 16K 792 -> 686, 1B at 32K 267 -> 232.
+//
+// Lane roles: scores use 8 lanes per position (lane u of the 8 takes dims
+// 64i + 8u .. +7 of 64-dim piece i), so a lane ends up with the scores of
+// positions 8g + lane/8; weighted values use R = D / 8 lanes per row (16
+// bytes, 8 dims, each), P = 64 / R rows per load.  The probabilities change
+// lanes through the wave's own LDS slot.
+template <int W, int D, int HG>
+__global__ __launch_bounds__(64 * W, HG >= 8 ? 1 : 2) void flowkv_chunk_kernel(const uint16_t* __restrict__ q,
+                                                                const uint16_t* __restrict__ K,
+                                                                const uint16_t* __restrict__ V, int64_t L, int j0,
+                                                                int j1, int chunk, float scale,
+                                                                float* __restrict__ work) {
   constexpr int kPart = D + 4;
-  // K and V rows in flight per lane: 4 for 512-byte rows (d = 256), 2 for
-  // 256-byte rows, where a deeper unroll measured slower.
-  constexpr int kFkvUnroll = D >= 256 ? 4 : 2;
-  constexpr int R = D / 8;        // lanes per V row (16 bytes each)
-  constexpr int P = 64 / R;       // V rows per wave load
-  __shared__ __attribute__((aligned(16))) uint32_t qs[HG][D / 2];   // query bf16 pairs
-  __shared__ float fs[CH][HG];                                       // scores, then exp(s - m_c)
-  __shared__ float red[4][HG];
-  __shared__ __attribute__((aligned(16))) float ys[4][HG][D];        // per-wave partial Y
+  constexpr int SP = kSubBytes / (2 * D);   // positions per sub-chunk
+  constexpr int NP = D / 64, NG = SP / 8;   // 64-dim pieces of a row, groups of 8 positions
+  constexpr int R = D / 8, P = 64 / R;
+  constexpr bool kQRegs = HG <= 4;          // the query in registers (64 of them at most), else in LDS
+  __shared__ __attribute__((aligned(16))) uint32_t qs[kQRegs ? 1 : HG][D / 2];
+  __shared__ __attribute__((aligned(16))) float fs[W][SP][HG];  // a sub-chunk's exp(s - m)
+  __shared__ float ms[W][HG], ls[W][HG];
+  __shared__ __attribute__((aligned(16))) float ys[W > 1 ? W : 1][W > 1 ? HG : 1][D];
 
   const int c = blockIdx.x, g = blockIdx.y, nchunks = gridDim.x;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int k0 = j0 + c * CH, n = min(j1 - k0, CH);   // positions k0 .. k0+n-1
-  const uint16_t* Kg = K + (size_t)g * L * D + (size_t)k0 * D;
-  const uint16_t* Vg = V + (size_t)g * L * D + (size_t)k0 * D;
-
-  // Lane roles: scores use 8 lanes per position (8 x 16 B = one 128-byte
-  // piece of the row per load; lane u of the 8 takes dims 64i + 8u .. +7),
-  // the weighted values R lanes per row (16 bytes, 8 dims, each).
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int u = lane & 7, kw = lane >> 3;
   const int rs = lane / R, db = lane % R;
-  // PRE: the whole chunk's K and V pieces of this lane are requested before
-  // the query is staged, so the three round trips overlap (the chunk's rows
-  // sit in registers: kSIt x D / 64 K pieces and CH / (4P) V pieces, rounded
-  // up; pieces past the chunk are not loaded).
-  constexpr int kSIt = (CH + 31) / 32;  // score passes of 32 positions (one, partly used, for CH = 16)
-  constexpr int kQPer = (HG * D / 2 + kFkvThreads - 1) / kFkvThreads;
-  constexpr int kKIt = PRE ? kSIt : 1, kKPc = PRE ? D / 64 : 1, kVIt = PRE ? (CH + 4 * P - 1) / (4 * P) : 1;
-  uint4 kreg[kKIt][kKPc], vreg[kVIt];
-  uint32_t qreg[kQPer];
-  if constexpr (PRE) {
-#pragma unroll
-    for (int o = 0; o < kQPer; ++o) {
-      const int e = tid + o * kFkvThreads;
-      if (e < HG * D / 2) {
-        const int h = e / (D / 2), p = e % (D / 2);
-        qreg[o] = reinterpret_cast<const uint32_t*>(q + (size_t)(g * HG + h) * D)[p];
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < kKIt; ++r) {
-      const int pl = (r * 4 + wave) * 8 + kw;
-#pragma unroll
-      for (int i = 0; i < kKPc; ++i)
-        kreg[r][i] = pl < n ? reinterpret_cast<const uint4*>(Kg + (size_t)pl * D)[8 * i + u] : uint4{0, 0, 0, 0};
-    }
-#pragma unroll
-    for (int it = 0; it < kVIt; ++it) {
-      const int pl = wave * P + rs + it * 4 * P;
-      vreg[it] = pl < n ? reinterpret_cast<const uint4*>(Vg + (size_t)pl * D)[db] : uint4{0, 0, 0, 0};
-    }
-#pragma unroll
-    for (int o = 0; o < kQPer; ++o) {
-      const int e = tid + o * kFkvThreads;
-      if (e < HG * D / 2) qs[e / (D / 2)][e % (D / 2)] = qreg[o];
-    }
-  } else {
-    for (int e = tid; e < HG * D / 2; e += kFkvThreads) {
-      const int h = e / (D / 2), p = e % (D / 2);
-      qs[h][p] = reinterpret_cast<const uint32_t*>(q + (size_t)(g * HG + h) * D)[p];
-    }
-  }
-  __syncthreads();
+  const int per = chunk / W;                                // a multiple of SP
+  const int k0 = j0 + c * chunk + wave * per;               // this wave's positions: k0 .. k0 + n - 1
+  const int n = max(0, min(j1 - k0, per));
+  const uint16_t* Kg = K + ((size_t)g * L + min(k0, j1 - 1)) * D;
+  const uint16_t* Vg = V + ((size_t)g * L + min(k0, j1 - 1)) * D;
+  const int last = max(n - 1, 0);
 
-  // Scores (Eq. 6).  (With PRE, kSIt <= kFkvUnroll: the loop unrolls fully
-  // and kreg is indexed by constants.)
-  static_assert(!PRE || kSIt <= kFkvUnroll, "PRE needs the score loop fully unrolled");
-#pragma unroll kFkvUnroll
-  for (int r = 0; r < kSIt; ++r) {
-    const int pl = (r * 4 + wave) * 8 + kw;
-    float acc[HG];
+  // Positions past the range read the last one; their scores are -inf.
+  uint4 kr[NG][NP], vr[8];
+  const auto load_k = [&](int p0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int h = 0; h < HG; ++h) acc[h] = 0.0f;
-    if (pl < n) {
-      const uint4* row = reinterpret_cast<const uint4*>(Kg + (size_t)pl * D);
+    for (int a = 0; a < NG; ++a) {
+      const uint4* row = reinterpret_cast<const uint4*>(Kg + (size_t)min(p0 + 8 * a + kw, last) * D);
 #pragma unroll
-      for (int i = 0; i < D / 64; ++i) {
-        uint4 kv;
-        if constexpr (PRE) kv = kreg[r][i];
-        else kv = row[8 * i + u];
-#pragma unroll
-        for (int h = 0; h < HG; ++h) {
-          const uint4 qv = *reinterpret_cast<const uint4*>(&qs[h][32 * i + 4 * u]);
-          acc[h] = dot2(kv.x, qv.x, acc[h]);
-          acc[h] = dot2(kv.y, qv.y, acc[h]);
-          acc[h] = dot2(kv.z, qv.z, acc[h]);
-          acc[h] = dot2(kv.w, qv.w, acc[h]);
-        }
-      }
-    }
-#pragma unroll
-    for (int h = 0; h < HG; ++h) {
-      float v = acc[h];
-      v += xor_lane<1>(v);
-      v += xor_lane<2>(v);
-      v += xor_lane<4>(v);
-      if (u == 0 && pl < CH) fs[pl][h] = pl < n ? v * scale : -INFINITY;
-    }
-  }
-  __syncthreads();
-
-  // Chunk max (Eq. 7), exponentials (Eq. 8) and their sum (Eq. 10);
-  // thread tid owns positions tid, tid + 256, ... below CH.
-  constexpr int kOwn = (CH + kFkvThreads - 1) / kFkvThreads;
-  float m[HG], l[HG];
-#pragma unroll
-  for (int h = 0; h < HG; ++h) {
-    float v = -INFINITY;
-#pragma unroll
-    for (int o = 0; o < kOwn; ++o)
-      if (tid + o * kFkvThreads < CH) v = fmaxf(v, fs[tid + o * kFkvThreads][h]);
-    v = wave_max(v);
-    if (lane == 0) red[wave][h] = v;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int h = 0; h < HG; ++h) m[h] = fmaxf(fmaxf(red[0][h], red[1][h]), fmaxf(red[2][h], red[3][h]));
-  __syncthreads();
-#pragma unroll
-  for (int h = 0; h < HG; ++h) {
-    float f = 0.0f;
-#pragma unroll
-    for (int o = 0; o < kOwn; ++o) {
-      const int p = tid + o * kFkvThreads;
-      if (p < CH) {
-        const float e = expf(fs[p][h] - m[h]);   // exp(-inf) = 0 past the range
-        fs[p][h] = e;
-        f += e;
-      }
-    }
-    const float sm = wave_sum(f);
-    if (lane == 0) red[wave][h] = sm;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int h = 0; h < HG; ++h) l[h] = (red[0][h] + red[1][h]) + (red[2][h] + red[3][h]);
-
-  // Weighted values (Eq. 11): wave w takes rows w*P + rs, then every 4P rows.
-  float y[HG][8];
-#pragma unroll
-  for (int h = 0; h < HG; ++h)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) y[h][e] = 0.0f;
-  // One V row piece (8 dims) of position pl into the weighted sums.
-  const auto vrow = [&](int pl, const uint4 w) __attribute__((always_inline)) {
-    const float v[8] = {bf16lo(w.x), bf16hi(w.x), bf16lo(w.y), bf16hi(w.y),
-                        bf16lo(w.z), bf16hi(w.z), bf16lo(w.w), bf16hi(w.w)};
-#pragma unroll
-    for (int h = 0; h < HG; ++h) {
-      const float f = fs[pl][h];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) y[h][e] = fmaf(f, v[e], y[h][e]);
+      for (int i = 0; i < NP; ++i) kr[a][i] = load_stream(row + 8 * i + u);
     }
   };
-  if constexpr (PRE) {
+  const auto load_v = [&](int p0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int it = 0; it < kVIt; ++it) {
-      const int pl = wave * P + rs + it * 4 * P;
-      if (pl < n) vrow(pl, vreg[it]);
-    }
-  } else {
-#pragma unroll kFkvUnroll
-    for (int pl = wave * P + rs; pl < n; pl += 4 * P) vrow(pl, reinterpret_cast<const uint4*>(Vg + (size_t)pl * D)[db]);
-  }
-  // Sum the P row slots of the wave (lanes db, db + R, ...), then the 4 waves.
-#pragma unroll
-  for (int h = 0; h < HG; ++h)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float v = y[h][e];
-      v = sum_lanes_from<R>(v);
-      y[h][e] = v;
-    }
-  if (rs == 0) {
+    for (int j = 0; j < 8; ++j)
+      vr[j] = load_stream(reinterpret_cast<const uint4*>(Vg + (size_t)min(p0 + P * j + rs, last) * D) + db);
+  };
+
+  uint4 qr[kQRegs ? HG : 1][kQRegs ? NP : 1];
+  if constexpr (kQRegs) {
 #pragma unroll
     for (int h = 0; h < HG; ++h)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) ys[wave][h][8 * db + e] = y[h][e];
+      for (int i = 0; i < NP; ++i) qr[h][i] = reinterpret_cast<const uint4*>(q + (size_t)(g * HG + h) * D)[8 * i + u];
   }
-  __syncthreads();
+  load_k(0);
+  load_v(0);
+  if constexpr (!kQRegs) {
+    for (int e = tid; e < HG * D / 2; e += 64 * W)
+      qs[e / (D / 2)][e % (D / 2)] = reinterpret_cast<const uint32_t*>(q + (size_t)(g * HG + e / (D / 2)) * D)[e % (D / 2)];
+    __syncthreads();
+  }
 
-  for (int e = tid; e < HG * D; e += kFkvThreads) {
-    const int h = e / D, dd = e % D;
-    float* part = work + ((size_t)(g * HG + h) * nchunks + c) * kPart;
-    part[4 + dd] = (ys[0][h][dd] + ys[1][h][dd]) + (ys[2][h][dd] + ys[3][h][dd]);
-    if (dd == 0) {
-      part[0] = m[h];
-      part[1] = l[h];
+  float m[HG], l[HG], y[HG][8];  // running state; l over the lane's own positions, y over its own rows
+#pragma unroll
+  for (int h = 0; h < HG; ++h) {
+    m[h] = -INFINITY;
+    l[h] = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[h][e] = 0.0f;
+  }
+  for (int p0 = 0; p0 < n; p0 += SP) {
+    // Scores (Eq. 6).
+    float s[HG][NG];
+#pragma unroll
+    for (int a = 0; a < NG; ++a)
+#pragma unroll
+      for (int h = 0; h < HG; ++h) {
+        float v = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+          uint4 qv;
+          if constexpr (kQRegs) qv = qr[h][i];
+          else qv = *reinterpret_cast<const uint4*>(&qs[h][32 * i + 4 * u]);
+          v = dot2(kr[a][i].x, qv.x, v);
+          v = dot2(kr[a][i].y, qv.y, v);
+          v = dot2(kr[a][i].z, qv.z, v);
+          v = dot2(kr[a][i].w, qv.w, v);
+        }
+        v += xor_lane<1>(v);
+        v += xor_lane<2>(v);
+        v += xor_lane<4>(v);
+        s[h][a] = p0 + 8 * a + kw < n ? v * scale : -INFINITY;
+      }
+    if (p0 + SP < n) load_k(p0 + SP);
+    // Running maximum (Eq. 7), exponentials (Eq. 8), correction (Eq. 9, 10).
+#pragma unroll
+    for (int h = 0; h < HG; ++h) {
+      float mx = s[h][0];
+#pragma unroll
+      for (int a = 1; a < NG; ++a) mx = fmaxf(mx, s[h][a]);
+      mx = fmaxf(mx, xor_lane<8>(mx));
+      mx = fmaxf(mx, xor_lane<16>(mx));
+      mx = fmaxf(mx, xor_lane<32>(mx));
+      mx = fmaxf(mx, m[h]);
+      const float base = mx == -INFINITY ? 0.0f : mx;  // no finite score yet: exp(-inf) = 0
+      const float corr = expf(m[h] - base);
+      m[h] = mx;
+      l[h] *= corr;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[h][e] *= corr;
+#pragma unroll
+      for (int a = 0; a < NG; ++a) {
+        const float f = expf(s[h][a] - base);
+        l[h] += f;
+        if (u == 0) fs[wave][8 * a + kw][h] = f;
+      }
+    }
+    // (A wave's LDS instructions are carried out in order; the fences keep the
+    // compiler from moving the accesses across.)
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    // Weighted values (Eq. 11).
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float* f = fs[wave][P * j + rs];
+      const float v[8] = {bf16lo(vr[j].x), bf16hi(vr[j].x), bf16lo(vr[j].y), bf16hi(vr[j].y),
+                          bf16lo(vr[j].z), bf16hi(vr[j].z), bf16lo(vr[j].w), bf16hi(vr[j].w)};
+#pragma unroll
+      for (int h = 0; h < HG; ++h)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) y[h][e] = fmaf(f[h], v[e], y[h][e]);
+    }
+    if (p0 + SP < n) load_v(p0 + SP);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  }
+
+  // Sum over the lanes: l over the positions (lanes kw), y over the rows of a
+  // load (lanes rs).
+#pragma unroll
+  for (int h = 0; h < HG; ++h) {
+    l[h] = sum_lanes_from<8>(l[h]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[h][e] = sum_lanes_from<R>(y[h][e]);
+  }
+  if constexpr (W == 1) {
+#pragma unroll
+    for (int h = 0; h < HG; ++h) {
+      float* part = work + ((size_t)(g * HG + h) * nchunks + c) * kPart;
+      if (rs == 0) {
+        reinterpret_cast<float4*>(part + 4 + 8 * db)[0] = make_float4(y[h][0], y[h][1], y[h][2], y[h][3]);
+        reinterpret_cast<float4*>(part + 4 + 8 * db)[1] = make_float4(y[h][4], y[h][5], y[h][6], y[h][7]);
+      }
+      if (lane == 0) {
+        part[0] = m[h];
+        part[1] = l[h];
+      }
+    }
+  } else {
+#pragma unroll
+    for (int h = 0; h < HG; ++h) {
+      if (rs == 0) {
+        reinterpret_cast<float4*>(&ys[wave][h][8 * db])[0] = make_float4(y[h][0], y[h][1], y[h][2], y[h][3]);
+        reinterpret_cast<float4*>(&ys[wave][h][8 * db])[1] = make_float4(y[h][4], y[h][5], y[h][6], y[h][7]);
+      }
+      if (lane == 0) {
+        ms[wave][h] = m[h];
+        ls[wave][h] = l[h];
+      }
+    }
+    __syncthreads();
+    // The waves' states merged in wave order (a wave without a finite score
+    // has weight 0).
+    for (int e = tid; e < HG * D; e += 64 * W) {
+      const int h = e / D, dd = e % D;
+      float mx = ms[0][h];
+#pragma unroll
+      for (int w = 1; w < W; ++w) mx = fmaxf(mx, ms[w][h]);
+      const float base = mx == -INFINITY ? 0.0f : mx;
+      float yt = 0.0f, lt = 0.0f;
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        const float a = expf(ms[w][h] - base);
+        yt = fmaf(a, ys[w][h][dd], yt);
+        lt = fmaf(a, ls[w][h], lt);
+      }
+      float* part = work + ((size_t)(g * HG + h) * nchunks + c) * kPart;
+      part[4 + dd] = yt;
+      if (dd == 0) {
+        part[0] = mx;
+        part[1] = lt;
+      }
     }
   }
 }
@@ -358,28 +370,34 @@ __global__ __launch_bounds__(kFkvThreads) void flowkv_merge_kernel(const float* 
   }
 }
 
-template <int CH, int D, int HG>
+// Waves per workgroup and positions per workgroup of phase 1.  Up to two
+// waves of one sub-chunk per CU: one wave and one sub-chunk each (latency is
+// the whole cost).  Beyond, four waves: the longest chunk up to 512 positions
+// that still gives every CU a workgroup, down to one sub-chunk per wave (two
+// workgroups per CU, so half the chunk and twice the partials to merge: 1-7%
+// slower over the Gemma3 stacks at 32K).
+struct FlowkvSplit {
+  int waves, chunk;
+};
+static FlowkvSplit flowkv_split(int64_t n, int G, int d, int cus) {
+  const int sp = kSubBytes / (2 * d);
+  if (ceil_div(n, sp) * G <= 2 * cus) return {1, sp};
+  int chunk = 512;
+  while (chunk > 4 * sp && ceil_div(n, chunk) * G < cus) chunk >>= 1;
+  return {4, chunk};
+}
+
+template <int D, int HG>
 static void launch_flowkv(const uint16_t* q, const uint16_t* K, const uint16_t* V, int64_t L, int G, int j0, int j1,
-                          float scale, float* work, void* out, int out_bf16, hipStream_t stream) {
-  const int nchunks = (int)ceil_div(j1 - j0, CH);
-  // Short ranges (at most 4096 positions, so chunks of 64 positions or fewer:
-  // the sliding-window layers), which are latency-bound, request each chunk's K
-  // and V with the query when there are at least 64 workgroups.  Measured on
-  // MI355X over the Gemma3 layer stacks at 32K, same bits: 27B (256
-  // workgroups per windowed layer) 3% and 4B (64) 2% faster.  Not with fewer
-  // workgroups (1B's windowed layers: the V requests then delay the scores on
-  // each CU's own bandwidth) nor on long ranges (1B's global layers also take
-  // 64-position chunks, 512 workgroups: 2-5% slower with the early requests).
-  bool pre = false;
-  if constexpr (CH <= 64) {
-    pre = (int64_t)nchunks * G >= 64 && j1 - j0 <= 4096;
-    if (pre)
-      hipLaunchKernelGGL((flowkv_chunk_kernel<CH, D, HG, true>), dim3(nchunks, G), dim3(kFkvThreads), 0, stream, q,
-                         K, V, L, j0, j1, scale, work);
-  }
-  if (!pre)
-    hipLaunchKernelGGL((flowkv_chunk_kernel<CH, D, HG, false>), dim3(nchunks, G), dim3(kFkvThreads), 0, stream, q, K,
-                       V, L, j0, j1, scale, work);
+                          float scale, float* work, void* out, int out_bf16, hipStream_t stream, int cus) {
+  const FlowkvSplit sp = flowkv_split(j1 - j0, G, D, cus);
+  const int nchunks = (int)ceil_div(j1 - j0, sp.chunk);
+  if (sp.waves == 1)
+    hipLaunchKernelGGL((flowkv_chunk_kernel<1, D, HG>), dim3(nchunks, G), dim3(64), 0, stream, q, K, V, L, j0, j1,
+                       sp.chunk, scale, work);
+  else
+    hipLaunchKernelGGL((flowkv_chunk_kernel<4, D, HG>), dim3(nchunks, G), dim3(256), 0, stream, q, K, V, L, j0, j1,
+                       sp.chunk, scale, work);
   // Dims per merge workgroup: halved (down to 16) until there are at least
   // 128 workgroups.
   const int H = G * HG;
@@ -411,42 +429,14 @@ static void launch_flowkv(const uint16_t* q, const uint16_t* K, const uint16_t* 
   }
 }
 
-// Chunk size: the largest of 512, 256, 128, 64 positions that still gives at
-// least two workgroups per CU; 32 where 64 leaves CUs without a workgroup,
-// and 16 where 32 still gives fewer than 64 workgroups.  (Measured on MI355X
-// over the Gemma3 layer stacks at 32K, windowed layers: the 4B stack 0.407 ms
-// at 64 positions (64 workgroups per layer), 0.376 at 32 (128), 0.378 at 16
-// (256); the 1B stack 0.287 ms at 64 (16 workgroups), 0.277 at 32 (32),
-// 0.255 at 16 (64); the 27B windowed layers, 256 workgroups at 64, went 3%
-// slower at 32.)
-static int flowkv_chunk(int64_t n, int G, int cus) {
-  for (int ch = 512; ch > 64; ch >>= 1)
-    if (ceil_div(n, ch) * G >= 2 * cus) return ch;
-  if (ceil_div(n, 64) * G >= cus) return 64;
-  return ceil_div(n, 32) * G >= 64 ? 32 : kMinChunk;
-}
-
-template <int D, int HG>
-static void launch_chunked(const uint16_t* q, const uint16_t* K, const uint16_t* V, int64_t L, int G, int j0, int j1,
-                           float scale, float* work, void* out, int out_bf16, hipStream_t stream, int cus) {
-  switch (flowkv_chunk(j1 - j0, G, cus)) {
-    case 512: launch_flowkv<512, D, HG>(q, K, V, L, G, j0, j1, scale, work, out, out_bf16, stream); break;
-    case 256: launch_flowkv<256, D, HG>(q, K, V, L, G, j0, j1, scale, work, out, out_bf16, stream); break;
-    case 128: launch_flowkv<128, D, HG>(q, K, V, L, G, j0, j1, scale, work, out, out_bf16, stream); break;
-    case 64: launch_flowkv<64, D, HG>(q, K, V, L, G, j0, j1, scale, work, out, out_bf16, stream); break;
-    case 32: launch_flowkv<32, D, HG>(q, K, V, L, G, j0, j1, scale, work, out, out_bf16, stream); break;
-    default: launch_flowkv<16, D, HG>(q, K, V, L, G, j0, j1, scale, work, out, out_bf16, stream); break;
-  }
-}
-
 template <int D>
 static bool dispatch_hg(int hg, const uint16_t* q, const uint16_t* K, const uint16_t* V, int64_t L, int G, int j0,
                         int j1, float scale, float* work, void* out, int out_bf16, hipStream_t stream, int cus) {
   switch (hg) {
-    case 1: launch_chunked<D, 1>(q, K, V, L, G, j0, j1, scale, work, out, out_bf16, stream, cus); return true;
-    case 2: launch_chunked<D, 2>(q, K, V, L, G, j0, j1, scale, work, out, out_bf16, stream, cus); return true;
-    case 4: launch_chunked<D, 4>(q, K, V, L, G, j0, j1, scale, work, out, out_bf16, stream, cus); return true;
-    case 8: launch_chunked<D, 8>(q, K, V, L, G, j0, j1, scale, work, out, out_bf16, stream, cus); return true;
+    case 1: launch_flowkv<D, 1>(q, K, V, L, G, j0, j1, scale, work, out, out_bf16, stream, cus); return true;
+    case 2: launch_flowkv<D, 2>(q, K, V, L, G, j0, j1, scale, work, out, out_bf16, stream, cus); return true;
+    case 4: launch_flowkv<D, 4>(q, K, V, L, G, j0, j1, scale, work, out, out_bf16, stream, cus); return true;
+    case 8: launch_flowkv<D, 8>(q, K, V, L, G, j0, j1, scale, work, out, out_bf16, stream, cus); return true;
     default: return false;
   }
 }
@@ -506,7 +496,7 @@ static q4nx_status flowkv_entry(const uint16_t* d_q, const uint16_t* d_k, const 
     return fail(Q4NX_ERR_BUFFER_TOO_SMALL, f + ": workspace smaller than q4nx_flowkv_workspace_size");
   const int cus = current_device_cus();
   if (!work) {
-    const size_t need = (size_t)H * (size_t)ceil_div(j1 - j0, flowkv_chunk(j1 - j0, (int)G, cus)) *
+    const size_t need = (size_t)H * (size_t)ceil_div(j1 - j0, flowkv_split(j1 - j0, (int)G, (int)d, cus).chunk) *
                         (size_t)(d + 4) * sizeof(float);
     if (need > kStaticScratchBytes)
       return fail(Q4NX_ERR_BUFFER_TOO_SMALL, f + ": the chunk partials (" + std::to_string(need) +

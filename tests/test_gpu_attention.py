@@ -111,3 +111,24 @@ def test_flowkv_bf16_output_and_repeatable(q4):
     ref, bound = decode_attention(q, K, V, t, 0, scale)
     got = o.float().cpu().numpy().astype(np.float64)
     assert (np.abs(got - ref) <= 2e-3 * bound + 1e-6 + 2.0 ** -8 * np.abs(ref)).all()
+
+
+# The edges of phase 1's split: one wave per workgroup with one, a whole and a
+# ragged sub-chunk (16, 32 and 64 positions for d = 256, 128 and 64), the last
+# shape that takes it and the first that takes four waves (n G = 512 sub-chunks
+# and one more position), four waves with empty ones in the last chunk, and
+# eight query heads per group (the query in LDS) at every d.
+@pytest.mark.parametrize("H,G,d,n", [(8, 4, 256, 16), (8, 4, 256, 17), (32, 16, 128, 31), (8, 8, 64, 65),
+                                     (8, 4, 256, 2048), (8, 4, 256, 2049), (16, 16, 128, 1024), (16, 16, 128, 1025),
+                                     (4, 1, 256, 8193), (8, 1, 256, 900), (8, 1, 128, 20000), (64, 8, 256, 4100),
+                                     (64, 8, 64, 4100)])
+def test_flowkv_split_edges(q4, H, G, d, n):
+    print("[case] flowkv split", H, G, d, n, flush=True)
+    q, K, V = _case(H, G, d, n + 3, seed=n)
+    scale = 1.0 / np.sqrt(d)
+    work = torch.full((q4.q4nx_flowkv_workspace_size(H, d, n) // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    o = torch.full((H, d), float("nan"), dtype=torch.float32, device="cuda")
+    q4.q4nx_flowkv_decode(_dev(q), _dev(K), _dev(V), H, G, d, n + 3, n - 1, 0, float(scale), o, work)
+    torch.cuda.synchronize()
+    ref, bound = decode_attention(q, K, V, n - 1, 0, scale)
+    assert (np.abs(o.cpu().numpy().astype(np.float64) - ref) <= 2e-3 * bound + 1e-6).all()
