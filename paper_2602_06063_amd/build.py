@@ -4,7 +4,8 @@
     python paper_2602_06063_amd/build.py --sanitize   # host-sanitized copy
 
 Every HIP source is compiled with packed-fp32 instructions disabled (the
-compiler otherwise forms v_pk_*_f32 from plain float code).
+compiler otherwise forms v_pk_*_f32 from plain float code), and with the
+leading scalar kernel arguments preloaded into registers.
 
 --sanitize builds _build/libq4nx_asan.so: the same sources with the host code
 (packer, validation, launch planning, launchers) instrumented with
@@ -52,6 +53,7 @@ def build(verbose: bool = False, sanitize: bool = False) -> str:
     cmd = [hipcc(), f"--offload-arch={ARCH}"] + opt + ["-std=c++17", "-fPIC", "-shared",
            "-Wall", "-Wno-unused-function", "-pthread",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "-mllvm", "-amdgpu-kernarg-preload-count=16",
            "-o", tmp] + srcs
     if verbose:
         print(" ".join(cmd), flush=True)

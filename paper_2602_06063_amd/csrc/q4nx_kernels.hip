@@ -510,22 +510,41 @@ struct GemvJob {
   const uint8_t* blob;
   const uint16_t* x;
   void* y;
-  int N, K, NS, KB;
-  int tq;        // row octets per row group (1, 2 or 4)
-  int nrg;       // row groups: NS * 4 / tq
-  int waves;     // waves splitting K (depends on K only)
+  int N, K;
+  int nrg;       // row groups of 8 * tq rows
   int nwg;       // workgroups of this job (each loops over row groups)
   int wg_begin;  // first workgroup of this job in the launch
   int pad;
 };
 
-struct GemvArgs {
-  GemvJob job[Q4NX_MAX_BATCH];
-  int njobs;
-  int y_bf16;
-  int chunk_blocks;  // blocks per chunk: a strip's weights are read through one descriptor per chunk
-  int pad;
+// The launch's first job travels as scalar kernel arguments, which gfx950
+// preloads into registers (the build's -amdgpu-kernarg-preload-count), so a
+// workgroup of it starts its first loads without a memory round trip for its
+// arguments; the workgroups of a batch's other jobs look theirs up in memory.
+struct GemvRest {
+  GemvJob job[Q4NX_MAX_BATCH - 1];
 };
+constexpr int kGemvBf16Out = 1, kGemvJobsShift = 1;  // flags: y is bf16, number of jobs
+
+// J holds the first job on entry.  The index first, then each field by itself:
+// selecting whole structures moves them to scratch memory, at 2.5 times the
+// cost of a launch.
+__device__ __forceinline__ void gemv_pick(GemvJob& J, int flags, const GemvRest& rest) {
+  const int wg = blockIdx.x;
+  if (wg < J.nwg) return;
+  int j = 0;
+#pragma unroll
+  for (int t = 1; t < Q4NX_MAX_BATCH - 1; ++t)
+    if (t + 1 < (flags >> kGemvJobsShift) && wg >= rest.job[t].wg_begin) j = t;
+  J.blob = rest.job[j].blob;
+  J.x = rest.job[j].x;
+  J.y = rest.job[j].y;
+  J.N = rest.job[j].N;
+  J.K = rest.job[j].K;
+  J.nrg = rest.job[j].nrg;
+  J.nwg = rest.job[j].nwg;
+  J.wg_begin = rest.job[j].wg_begin;
+}
 
 // Registers of one in-flight block: TQ row octets of codes, scales, offsets
 // (E8M0 scale bytes and no offsets for the MXFP4 variant).
@@ -655,38 +674,38 @@ __device__ __forceinline__ void gemv_compute(const GemvSlot<TQ>& R, bool gvalid,
 }
 
 template <int TQ, int D, int F>
-__global__ __launch_bounds__(64 * kGemvMaxWaves) void gemv_kernel(const GemvArgs args) {
+__global__ __launch_bounds__(64 * kGemvMaxWaves) void gemv_kernel(
+    const uint8_t* blob0, const uint16_t* x0, void* y0, int N0, int K0, int nrg0, int nwg0, int waves, int flags,
+    const GemvRest rest) {
   constexpr int kBytes = wblock_bytes<F>();
   // red: the waves' row sums; xw: each wave's x slot (one block of x).
   __shared__ float red[kRedFloats];
   __shared__ __attribute__((aligned(16))) uint32_t xw_all[kGemvMaxWaves][kGroupsPerRow * kGroupPadDw];
 
-  const int wg = blockIdx.x;
-  int jb = 0;
-#pragma unroll
-  for (int t = 1; t < Q4NX_MAX_BATCH; ++t)
-    if (t < args.njobs && wg >= args.job[t].wg_begin) jb = t;
-  const GemvJob& J = args.job[jb];
+  GemvJob J = {blob0, x0, y0, N0, K0, nrg0, nwg0, 0, 0};
+  gemv_pick(J, flags, rest);
+  const int wg = blockIdx.x, KB = (J.K + kBlockCols - 1) / kBlockCols;
+  const bool y_bf16 = flags & kGemvBf16Out;
 
   // The wave index is uniform across a wave; saying so keeps every block
   // offset and branch derived from it in scalar registers.
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 7;
-  const int W = J.waves;
+  const int W = waves;
   const bool wave_on = w < W;  // wave-uniform
-  const int CB = args.chunk_blocks;
-  const int nchunks = (J.KB + CB - 1) / CB;
+  constexpr int CB = kGemvChunkBlocks;
+  const int nchunks = (KB + CB - 1) / CB;
   uint32_t* const xw = xw_all[wave_on ? w : 0];
 
   for (int rg = wg - J.wg_begin; rg < J.nrg; rg += J.nwg) {
     const int row0 = rg * 8 * TQ;
     const int strip = row0 >> 5, t0 = (row0 & 31) >> 3;
-    const uint8_t* sblob = J.blob + (size_t)strip * J.KB * kBytes;
+    const uint8_t* sblob = J.blob + (size_t)strip * KB * kBytes;
     float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 
     for (int ch = 0; ch < nchunks; ++ch) {
       const int jc0 = ch * CB;
-      const int nb = min(CB, J.KB - jc0);
+      const int nb = min(CB, KB - jc0);
       const __amdgpu_buffer_rsrc_t rs = chunk_rsrc(sblob + (size_t)jc0 * kBytes, nb * kBytes);
       const int kvalid = J.K - jc0 * kBlockCols;  // columns of this chunk inside K
       const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
@@ -738,7 +757,7 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void gemv_kernel(const GemvArgs
       for (int q = 0; q < W; ++q) sum += red[q * 32 + threadIdx.x];
       const int64_t n = (int64_t)row0 + threadIdx.x;
       if (n < J.N) {
-        if (args.y_bf16)
+        if (y_bf16)
           static_cast<uint16_t*>(J.y)[n] = f32_to_bf16_bits(sum);
         else
           static_cast<float*>(J.y)[n] = sum;
@@ -758,24 +777,25 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void gemv_kernel(const GemvArgs
 // gemv_kernel (same waves per row group), hence the same bits.  Every wave
 // meets the same barriers: two per row group.
 template <int TQ, int D, int F>
-__global__ __launch_bounds__(64 * kGemvMaxWaves) void gemv_stream_kernel(const GemvArgs args) {
+__global__ __launch_bounds__(64 * kGemvMaxWaves) void gemv_stream_kernel(
+    const uint8_t* blob0, const uint16_t* x0, void* y0, int N0, int K0, int nrg0, int nwg0, int waves, int flags,
+    const GemvRest rest) {
   constexpr int kBytes = wblock_bytes<F>();
   __shared__ float red[kRedFloats];
   __shared__ __attribute__((aligned(16))) uint32_t xw_all[kGemvMaxWaves][kGroupsPerRow * kGroupPadDw];
 
-  const int wg = blockIdx.x;
-  int jb = 0;
-#pragma unroll
-  for (int t = 1; t < Q4NX_MAX_BATCH; ++t)
-    if (t < args.njobs && wg >= args.job[t].wg_begin) jb = t;
-  const GemvJob& J = args.job[jb];
+  GemvJob J = {blob0, x0, y0, N0, K0, nrg0, nwg0, 0, 0};
+  gemv_pick(J, flags, rest);
+  const int wg = blockIdx.x, KB = (J.K + kBlockCols - 1) / kBlockCols;
+  const bool y_bf16 = flags & kGemvBf16Out;
 
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 7;
-  const int W = J.waves, nb = J.KB;
+  const int W = waves, nb = KB;
   const bool wave_on = w < W;  // wave-uniform
   const int r0 = wg - J.wg_begin;
-  const int nrg = r0 < J.nrg ? (J.nrg - 1 - r0) / J.nwg + 1 : 0;  // row groups of this workgroup
+  // Row groups of this workgroup (one each unless there are more than the grid holds).
+  const int nrg = r0 >= J.nrg ? 0 : J.nwg == J.nrg ? 1 : (J.nrg - 1 - r0) / J.nwg + 1;
   if (nrg == 0) return;                                           // the whole workgroup
   const int nbw = wave_on ? (nb - w + W - 1) / W : 0;              // this wave's blocks per row group
   const int Q = nbw * nrg;
@@ -826,7 +846,7 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void gemv_stream_kernel(const G
       for (int q = 0; q < W; ++q) sum += red[q * 32 + threadIdx.x];
       const int64_t n = (int64_t)(r0 + k * J.nwg) * 8 * TQ + threadIdx.x;
       if (n < J.N) {
-        if (args.y_bf16)
+        if (y_bf16)
           static_cast<uint16_t*>(J.y)[n] = f32_to_bf16_bits(sum);
         else
           static_cast<float*>(J.y)[n] = sum;
@@ -2765,35 +2785,27 @@ static q4nx_status gemv_launch(const q4nx_gemv_desc* descs, int count, q4nx_dtyp
   const int tq = streaming ? 2 : gemv_tq(strips);
   int waves = streaming ? 8 : gemv_waves(strips * (4 / tq), min_kb);
   while (waves > 1 && waves > min_kb) waves >>= 1;
-  GemvArgs args = {};
-  args.njobs = count;
-  args.y_bf16 = (y_dtype == Q4NX_BF16);
+  GemvJob jobs[Q4NX_MAX_BATCH] = {};
   int64_t wg = 0;
-  int max_waves = 1;
   for (int i = 0; i < count; ++i) {
     const q4nx_gemv_desc& d = descs[i];
-    GemvJob& J = args.job[i];
+    GemvJob& J = jobs[i];
     J.blob = static_cast<const uint8_t*>(d.blob);
     J.x = d.x;
     J.y = d.y;
     J.N = (int)d.N;
     J.K = (int)d.K;
-    J.NS = (int)ceil_div(d.N, kBlockRows);
-    J.KB = (int)ceil_div(d.K, kBlockCols);
-    J.tq = tq;
-    J.nrg = J.NS * (4 / tq);
-    J.waves = waves;
+    J.nrg = (int)ceil_div(d.N, kBlockRows) * (4 / tq);
     // One workgroup per row group (the hardware keeps every CU fed as
     // workgroups retire); the loop over row groups only engages past 2^20.
     J.nwg = std::min(J.nrg, 1 << 20);
     J.wg_begin = (int)wg;
     wg += J.nwg;
-    max_waves = std::max(max_waves, J.waves);
-    args.chunk_blocks = std::max(args.chunk_blocks, std::min(J.KB, kGemvChunkBlocks));
   }
+  const int flags = (y_dtype == Q4NX_BF16 ? kGemvBf16Out : 0) | count << kGemvJobsShift;
   // LDS of both kernels (static): the row sums and one x slot per wave.
   constexpr int64_t lds = sizeof(float) * (kRedFloats + kGemvMaxWaves * kGroupsPerRow * kGroupPadDw);
-  const dim3 block(64 * max_waves);
+  const dim3 block(64 * waves);
   if (streaming) {
     // Streaming form: a bounded grid (workgroups per CU as the LDS allows, at
     // most kGemvStreamPerCu), dealt to the jobs in proportion to their row
@@ -2802,20 +2814,24 @@ static q4nx_status gemv_launch(const q4nx_gemv_desc* descs, int count, q4nx_dtyp
     const int64_t total_rg = strips * (4 / tq), budget = (int64_t)device_cus() * per_cu;
     int64_t sw = 0;
     for (int i = 0; i < count; ++i) {
-      GemvJob& J = args.job[i];
+      GemvJob& J = jobs[i];
       J.nwg = (int)std::max<int64_t>(1, std::min<int64_t>(J.nrg, (budget * J.nrg + total_rg - 1) / total_rg));
       J.wg_begin = (int)sw;
       sw += J.nwg;
     }
-    hipLaunchKernelGGL((gemv_stream_kernel<2, kGemvDepth2, F>), dim3((unsigned)sw), block, 0, stream, args);
-    return check_launch(fn);
+    wg = sw;
   }
-  const dim3 grid((unsigned)wg);
-  switch (tq) {  // x is staged per wave in static LDS
-    case 4: hipLaunchKernelGGL((gemv_kernel<4, kGemvDepth4, F>), grid, block, 0, stream, args); break;
-    case 2: hipLaunchKernelGGL((gemv_kernel<2, kGemvDepth2, F>), grid, block, 0, stream, args); break;
-    default: hipLaunchKernelGGL((gemv_kernel<1, kGemvDepth1, F>), grid, block, 0, stream, args); break;
-  }
+  GemvRest rest;
+  std::copy(jobs + 1, jobs + Q4NX_MAX_BATCH, rest.job);
+  const GemvJob& J = jobs[0];
+  const auto launch = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)wg), block, 0, stream, J.blob, J.x, J.y, J.N, J.K, J.nrg, J.nwg, waves,
+                       flags, rest);
+  };
+  if (streaming) launch(gemv_stream_kernel<2, kGemvDepth2, F>);
+  else if (tq == 4) launch(gemv_kernel<4, kGemvDepth4, F>);  // x is staged per wave in static LDS
+  else if (tq == 2) launch(gemv_kernel<2, kGemvDepth2, F>);
+  else launch(gemv_kernel<1, kGemvDepth1, F>);
   return check_launch(fn);
 }
 
