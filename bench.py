@@ -582,7 +582,7 @@ def traffic_file(config):
 
 # The prefill step's launches: the products, their partial sums and the
 # dequant pass of products that dequantize first.
-PREFILL_KERNELS = ("gemm256_kernel", "gemm256x128_kernel", "gemm_kernel", "splitk_sum_kernel", "dequant_kernel")
+PREFILL_KERNELS = ("gemm256_kernel", "gemm_tile_kernel", "gemm_ks_kernel", "gemm_kernel", "splitk_sum_kernel", "dequant_kernel")
 
 
 def kernel_family(name):
@@ -1361,7 +1361,7 @@ def main():
         if gemm_only_ms:
             t = gemm_only_ms
             result["roofline"]["dominant_kernel"] = {
-                "what": "the same products' bf16 MFMA launches alone (gemm256_kernel, gemm256x128_kernel, "
+                "what": "the same products' bf16 MFMA launches alone (gemm256_kernel, gemm_tile_kernel, "
                         "gemm_kernel and the split-K sum, the dequantization pass excluded): HIP events around every q4nx_gemm_bf16 call of "
                         "the two-phase step, summed per step, median over the steps",
                 "ms_median": round(t, 4), "achieved": round(pre_flops / (t * 1e-3) / 1e12, 2),

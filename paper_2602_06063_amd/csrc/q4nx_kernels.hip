@@ -1937,7 +1937,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_kernel(
 // ---- few rows: K split over the waves of a workgroup -------------------------
 // For products with too few tiles of the kernels above to fill the CUs: short
 // prompts, batches of decoding users, the last chunk of a prompt.  There the
-// latency of the operand loads bounds the general kernel (one K step of a
+// latency of the operand loads bounds gemm_kernel (one K step of a
 // 128 x 64 tile took 0.7 us with 8 us of matrix work in 256 of them).  A
 // workgroup owns 16 MT rows x 16 NT outputs and all of K; its W waves deal the
 // 128-column units of K out among themselves (unit u to wave u % W), each wave
@@ -1955,7 +1955,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_kernel(
 // lane, took 20 instead of 16 us on a 32-row tile: the address unit handles
 // such a load at a quarter of the rate.)  A wave's LDS instructions are
 // carried out in order, so one slot per wave is enough.
-// Measured on MI355X, Q4NX weights (general kernel's plan -> this one, us):
+// Measured on MI355X, Q4NX weights (plans of gemm_kernel -> this one, us):
 // Gemma3-1B at 16 rows q/k/v 14.7 -> 4.2, o 13.4 -> 4.0, gate/up 16.4 -> 7.1,
 // down 67.5 -> 9.0; 4B at 77 rows 29.0 -> 9.7, 23.9 -> 6.9, 41.5 -> 30.9,
 // 100 -> 18.4.  Whole calls through q4nx_gemm_ex: eight 1B layers at 16 rows
@@ -2180,9 +2180,9 @@ __global__ __launch_bounds__(64 * W, MT * NT >= 16 || MT > 4 ? 1 : 2) void gemm_
 
 // ---- launch planning ----------------------------------------------------------
 // Tile shapes of the plan: 0 = 256 x 256, 1 = 256 x 128, 2 = 128 x 128, 3 =
-// 128 x 64, as the general kernel (256 x 256: gemm256_kernel) computes them;
+// 128 x 64, as gemm_kernel (256 x 256: gemm256_kernel) computes them;
 // where K allows, gemm_tile_kernel takes a region over (see kPlanWide).  The
-// round costs below were measured with the general kernel.
+// round costs below were measured with gemm_kernel.
 struct GemmTile {
   int bm, bn;
   float round_cost;  // time of one full round (a tile on every CU), relative to shape 0
