@@ -1961,6 +1961,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_kernel(
 // 100 -> 18.4.  Whole calls through q4nx_gemm_ex: eight 1B layers at 16 rows
 // 869 -> 278 us (then bound by the caller), four 4B layers at 77 rows 816 ->
 // 269 us, two at 512 rows 541 -> 327 us.
+// Tiles of 80 and 96 columns: an X fragment read and an X row staged serve more
+// outputs, and products of many columns take one round of tiles where 64 columns
+// needed two.  4B gate/up at 77 rows 31.1 -> 21.5 us, 27B gate/up at 77 rows 96
+// -> 77, 27B o at 300 rows 31.8 -> 29.7 (MXFP4 28.0 -> 25.3).  (128 columns
+// spill or were slower.)
 // The order of every sum is fixed by M, N and K, and is the same for the three
 // weight operands, so they agree bit for bit on the same bf16 weights.
 constexpr int kKsUnit = 128;              // columns of K per unit
@@ -2374,9 +2379,10 @@ struct KsTile {
   int mt, nt, waves;
   float fixed_us, unit_us;
 };
-constexpr KsTile kKsTiles[] = {{1, 1, 8, 1.0f, 0.09f}, {1, 2, 4, 1.0f, 0.15f}, {2, 2, 4, 0.9f, 0.18f}, {3, 2, 4, 1.6f, 0.23f},
+constexpr KsTile kKsTiles[] = {{1, 1, 8, 1.0f, 0.09f}, {1, 2, 4, 1.0f, 0.15f}, {2, 2, 4, 0.9f, 0.18f}, {3, 2, 4, 1.6f, 0.24f},
                                {2, 4, 4, 1.8f, 0.31f}, {3, 4, 4, 3.4f, 0.36f}, {4, 4, 4, 4.4f, 0.40f}, {5, 4, 4, 4.8f, 0.50f},
-                               {6, 4, 4, 5.1f, 0.57f}, {8, 4, 4, 6.6f, 0.675f}};
+                               {6, 4, 4, 5.1f, 0.57f}, {8, 4, 4, 6.6f, 0.675f}, {4, 5, 4, 6.0f, 0.49f}, {5, 5, 4, 7.0f, 0.55f},
+                               {4, 6, 4, 6.0f, 0.58f}, {5, 6, 4, 6.5f, 0.65f}, {6, 6, 4, 7.2f, 0.70f}};
 constexpr int kKsConfigs = (int)(sizeof(kKsTiles) / sizeof(kKsTiles[0]));
 constexpr double kKsLaunchUs = 3.2;
 constexpr int64_t kKsMaxTiles = 16384;  // beyond it the chip is full many times over
@@ -2466,9 +2472,12 @@ static int ks_choose(int64_t M, int64_t N, int64_t K, int cus, double best) {
     const KsTile& t = kKsTiles[i];
     const int64_t tiles = ceil_div(M, 16 * t.mt) * ceil_div(N, 16 * t.nt);
     if (tiles > kKsMaxTiles) continue;
-    // Small tiles share a CU, so a part of a round costs its share.
-    double load = std::max(1.0, (double)tiles / cus);
-    if (t.mt * t.nt >= 16) load = std::ceil(load);
+    // A CU with one tile more than the others takes that much longer, and of
+    // the small tiles, two of which share a CU, nearly so: 1.25 rounds of them
+    // measured 1.72-1.93 times one, 1.5 rounds 1.78-1.88, 2.5 rounds 2.75-2.9.
+    const double full = (double)(tiles / cus), u = (double)tiles / cus - full;
+    double load = full + (u > 0.0 ? t.mt * t.nt >= 16 ? 1.0 : 0.75 + 0.25 * u : 0.0);
+    load = std::max(1.0, load);
     const double c = kKsLaunchUs + load * (t.fixed_us + units * t.unit_us);
     if (c < best) {
       best = c;
@@ -2617,8 +2626,8 @@ static q4nx_status launch_ks(int64_t M, int64_t N, int64_t K, const uint16_t* X,
 }
 
 // The product by gemm_ks_kernel with tile `cfg` of kKsTiles.  bf16 weights
-// take more LDS per unit: their tiles stop at 64 x 64 (the same waves, hence
-// the same bits).
+// take more LDS per unit: their tiles stop at 64 x 64 (the same waves and
+// units, hence the same bits).
 template <int WF>
 static q4nx_status launch_ks_config(int cfg, int64_t M, int64_t N, int64_t K, const uint16_t* X, const void* w,
                                     void* Y, int y_bf16, hipStream_t stream) {
@@ -2633,7 +2642,12 @@ static q4nx_status launch_ks_config(int cfg, int64_t M, int64_t N, int64_t K, co
     case 6: return launch_ks<4, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
     case 7: return launch_ks<big ? 5 : 4, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
     case 8: return launch_ks<big ? 6 : 4, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
-    default: return launch_ks<big ? 8 : 4, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
+    case 9: return launch_ks<big ? 8 : 4, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
+    case 10: return launch_ks<4, big ? 5 : 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
+    case 11: return launch_ks<big ? 5 : 4, big ? 5 : 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
+    case 12: return launch_ks<4, big ? 6 : 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
+    case 13: return launch_ks<big ? 5 : 4, big ? 6 : 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
+    default: return launch_ks<big ? 6 : 4, big ? 6 : 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
   }
 }
 

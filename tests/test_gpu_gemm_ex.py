@@ -284,7 +284,10 @@ def test_gemm_ex_split_repeats_with_workspace_cleared(q4):
 # one unit, and many units.
 FEW_ROWS = [(16, 100, 1184), (1, 6001, 1184), (34, 3001, 1184), (47, 6001, 1184), (145, 2501, 1184),
             (67, 8001, 1184), (193, 4001, 1184), (145, 6001, 1184), (163, 6001, 1184), (193, 6001, 1184),
-            (3, 40, 32), (17, 33, 128), (77, 2560, 10272)]
+            (3, 40, 32), (17, 33, 128), (77, 2560, 10272),
+            # the tiles of 80 x 64, 128 x 64 and those of 80 and 96 columns, K ending inside a unit
+            (65, 12001, 672), (110, 15001, 1184), (49, 18001, 672), (65, 18001, 672), (49, 24001, 672), (65, 24001, 672),
+            (163, 10001, 672)]
 
 
 @pytest.mark.parametrize("M,N,K", FEW_ROWS)
