@@ -2513,7 +2513,13 @@ static GemmChoice gemm_choose(int wf, int64_t M, int64_t N, int64_t K, bool have
   c.two_phase = have_work && wf == kWQ4NX && deq_us < extra * kloop_us;
   c.w_bytes = c.two_phase ? (size_t)ceil_div(N * K * 2, 256) * 256 : 0;
   double best = plan_us(c.plan, c.count, K, cus), wide = 0.0;
-  if (wide_ok(K)) {
+  // One chain over all of K does not take the place of a split one, although it
+  // may be a few percent faster (699 -> 681 us on one product): its float32
+  // sums are longer, and the error against 64 bits went from 3.4e-7 to 6.2e-7.
+  // (gemm_ks_kernel's four sums are shorter than the segments'.)
+  bool split = false;
+  for (int i = 0; i < c.count; ++i) split = split || c.plan[i].ks > 1;
+  if (wide_ok(K) && !split) {
     const int n = wide_plan(M, N, K, cus, true, c.wide, &wide);
     if (wide <= best) {
       best = wide;
