@@ -208,6 +208,13 @@ __global__ __launch_bounds__(64 * W, HG >= 8 ? 1 : 2) void flowkv_chunk_kernel(c
     // (A wave's LDS instructions are carried out in order; the fences keep the
     // compiler from moving the accesses across.)
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    // Rows past the range are copies of the last one with weight 0, which
+    // times an infinity would be NaN.
+    if (p0 + SP > n) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (p0 + P * j + rs >= n) vr[j] = make_uint4(0, 0, 0, 0);
+    }
     // Weighted values (Eq. 11).
 #pragma unroll
     for (int j = 0; j < 8; ++j) {

@@ -132,3 +132,23 @@ def test_flowkv_split_edges(q4, H, G, d, n):
     torch.cuda.synchronize()
     ref, bound = decode_attention(q, K, V, n - 1, 0, scale)
     assert (np.abs(o.cpu().numpy().astype(np.float64) - ref) <= 2e-3 * bound + 1e-6).all()
+
+
+# Ranges that end inside a sub-chunk, one wave and four waves per workgroup:
+# the lanes past the end must not weigh the last row again, where 0 times an
+# infinity would be NaN.
+@pytest.mark.parametrize("H,G,d,n", [(8, 4, 256, 17), (8, 8, 64, 70), (16, 4, 128, 2500)])
+def test_flowkv_infinite_last_value(q4, H, G, d, n):
+    print("[case] flowkv infinite value", H, G, d, n, flush=True)
+    q, K, V = _case(H, G, d, n, seed=d)
+    V[:, n - 1, 3], V[:, n - 1, 5] = 0x7F80, 0xFF80  # +inf, -inf
+    scale = 1.0 / np.sqrt(d)
+    work = torch.full((q4.q4nx_flowkv_workspace_size(H, d, n) // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    o = torch.empty((H, d), dtype=torch.float32, device="cuda")
+    q4.q4nx_flowkv_decode(_dev(q), _dev(K), _dev(V), H, G, d, n, n - 1, 0, float(scale), o, work)
+    got = o.cpu().numpy().astype(np.float64)
+    assert (got[:, 3] == np.inf).all() and (got[:, 5] == -np.inf).all()
+    V[:, n - 1, 3] = V[:, n - 1, 5] = 0
+    ref, bound = decode_attention(q, K, V, n - 1, 0, scale)
+    rest = np.delete(np.arange(d), [3, 5])
+    assert (np.abs(got - ref)[:, rest] <= 2e-3 * bound[:, rest] + 1e-6).all()
