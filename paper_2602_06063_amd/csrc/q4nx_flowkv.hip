@@ -29,7 +29,12 @@ namespace q4nx {
 typedef __bf16 bf16x2f __attribute__((ext_vector_type(2)));
 
 constexpr int kMinChunk = 16;      // smallest chunk: sizes the workspace
-constexpr int kSubBytes = 8192;    // K (and V) bytes a wave takes at a time
+// Positions a wave takes at a time: 4 KiB of K (and of V), at least 16
+// positions.  (8 KiB at d = 64 and 128 kept the workgroups of short ranges to
+// half and their waves to twice the serial work: 8 heads in one group at
+// d = 64 over 100 positions 13.5 us, now 7.7; 4 KiB at d = 256 would halve the
+// loads in flight of the ranges that stream.)
+constexpr int sub_positions(int d) { return d >= 128 ? 16 : 2048 / d; }
 constexpr int kFkvThreads = 256;   // merge workgroups
 constexpr int kMergeRegs = 8;      // chunks per slice the one-pass merge holds in registers
 
@@ -69,41 +74,85 @@ __device__ __forceinline__ float sum_lanes_from(float v) {
   return v + xor_lane<32>(v);
 }
 
+// The 8 lanes u of a position each hold a part of H * A values (H heads, A
+// groups of positions); their sums are formed and shared out over the lanes:
+// the low bits of u pick the head, the next ones the group, and lanes that are
+// left over hold the same sums.  Lanes 1, 2 and 4 apart are added in turn (M),
+// each step halving the values that a lane still holds.
+template <int M, int H, int A, int NR>
+__device__ __forceinline__ void scatter_sum(const float* v, float* out, int u) {
+  const bool up = u & M;
+  if constexpr (M == 8) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i) out[i] = v[i];
+  } else if constexpr (H > 1) {
+    float w[H / 2 * A];
+#pragma unroll
+    for (int h = 0; h < H / 2; ++h)
+#pragma unroll
+      for (int a = 0; a < A; ++a) {
+        const float x0 = v[2 * h * A + a], x1 = v[(2 * h + 1) * A + a];
+        w[h * A + a] = (up ? x1 : x0) + xor_lane<M>(up ? x0 : x1);
+      }
+    scatter_sum<2 * M, H / 2, A, NR>(w, out, u);
+  } else if constexpr (A > 1) {
+    float w[A / 2];
+#pragma unroll
+    for (int a = 0; a < A / 2; ++a) {
+      const float x0 = v[2 * a], x1 = v[2 * a + 1];
+      w[a] = (up ? x1 : x0) + xor_lane<M>(up ? x0 : x1);
+    }
+    scatter_sum<2 * M, 1, A / 2, NR>(w, out, u);
+  } else {
+    const float w = v[0] + xor_lane<M>(v[0]);
+    scatter_sum<2 * M, 1, 1, NR>(&w, out, u);
+  }
+}
+
 // Phase 1.  grid (chunks, G), W waves: workgroup (c, g) covers `chunk`
 // positions from j0 + c chunk, each wave a contiguous part of them, for the HG
 // query heads of group g.  Partial of (head, chunk) at
 // work[(head * nchunks + chunk) * (D + 4)]: m_c, l_c, -, -, Y_c[D].
 //
-// A wave walks its part in sub-chunks of SP = 4096 / D positions (8 KiB of K
-// and of V: eight 16-byte loads per lane each) with FlowKV's running state
-// (Eq. 7-11), no barrier and no workgroup-wide phase: K of the next sub-chunk
-// is requested as soon as the scores are out of its registers, V as soon as
-// the weighted sums are, so the wave always has loads in flight; the waves'
-// states are merged at the end, through LDS.  Short ranges (the sliding-window
-// layers) are bound by latency and take one wave and one sub-chunk per
-// workgroup: one round trip for q, K and V together, and none of the six
-// barriers of a workgroup that forms one softmax.  Measured on MI355X over the
-// Gemma3 layer stacks against such workgroups (us): 4B at 32K 386 -> 332, at
-// 1024 270 -> 224, 27B at 16K 792 -> 686, 1B at 32K 267 -> 232.
+// A wave walks its part in sub-chunks of SP positions (sub_positions below)
+// with FlowKV's running state (Eq. 7-11), no barrier and no workgroup-wide
+// phase: K of the next sub-chunk is requested as soon as the scores are out of
+// its registers, V as soon as the weighted sums are, so the wave always has
+// loads in flight; the waves' states are merged at the end, through LDS.
+// Short ranges (the sliding-window layers) are bound by latency and take one
+// sub-chunk per wave: one round trip for q, K and V together, and none of the
+// six barriers of a workgroup that forms one softmax.
 //
 // Lane roles: scores use 8 lanes per position (lane u of the 8 takes dims
-// 64i + 8u .. +7 of 64-dim piece i), so a lane ends up with the scores of
-// positions 8g + lane/8; weighted values use R = D / 8 lanes per row (16
-// bytes, 8 dims, each), P = 64 / R rows per load.  The probabilities change
+// 64i + 8u .. +7 of 64-dim piece i).  scatter_sum leaves each lane the scores
+// of one head and of its share of the positions 8a + lane/8, so that every
+// exponential is taken once and a lane keeps the running maximum of one head.
+// (With the sums left in all 8 lanes, each of them took the exponentials of
+// every head: 16 heads in 2 groups at d = 256 over 9000 positions ran 27.5 us
+// where a workgroup that forms one softmax took 20.3; now 16.4.)  Weighted
+// values use R = D / 8 lanes per row (16 bytes, 8 dims, each), P = 64 / R rows
+// per load.  The probabilities, and the correction of the heads' sums, change
 // lanes through the wave's own LDS slot.
 template <int W, int D, int HG>
-__global__ __launch_bounds__(64 * W, HG >= 8 ? 1 : 2) void flowkv_chunk_kernel(const uint16_t* __restrict__ q,
+__global__ __launch_bounds__(64 * W, HG >= 8 && D >= 256 ? 1 : 2) void flowkv_chunk_kernel(const uint16_t* __restrict__ q,
                                                                 const uint16_t* __restrict__ K,
                                                                 const uint16_t* __restrict__ V, int64_t L, int j0,
                                                                 int j1, int chunk, float scale,
                                                                 float* __restrict__ work) {
   constexpr int kPart = D + 4;
-  constexpr int SP = kSubBytes / (2 * D);   // positions per sub-chunk
+  constexpr int SP = sub_positions(D);
   constexpr int NP = D / 64, NG = SP / 8;   // 64-dim pieces of a row, groups of 8 positions
-  constexpr int R = D / 8, P = 64 / R;
+  constexpr int R = D / 8, P = 64 / R, NV = SP / P;
   constexpr bool kQRegs = HG <= 4;          // the query in registers (64 of them at most), else in LDS
+  // Scores per lane after scatter_sum: head u % HG, and kSplit further bits of
+  // u as the low bits of the group.
+  constexpr int kHBits = HG == 8 ? 3 : HG == 4 ? 2 : HG == 2 ? 1 : 0;
+  constexpr int kSplit = std::min(3 - kHBits, NG == 2 ? 1 : 2);
+  constexpr int NR = NG >> kSplit;
+  static_assert(NG == 2 || NG == 4, "groups of a sub-chunk");
   __shared__ __attribute__((aligned(16))) uint32_t qs[kQRegs ? 1 : HG][D / 2];
   __shared__ __attribute__((aligned(16))) float fs[W][SP][HG];  // a sub-chunk's exp(s - m)
+  __shared__ __attribute__((aligned(16))) float cs[W][HG];      // its correction exp(m_left - m)
   __shared__ float ms[W][HG], ls[W][HG];
   __shared__ __attribute__((aligned(16))) float ys[W > 1 ? W : 1][W > 1 ? HG : 1][D];
 
@@ -120,7 +169,7 @@ __global__ __launch_bounds__(64 * W, HG >= 8 ? 1 : 2) void flowkv_chunk_kernel(c
   const int last = max(n - 1, 0);
 
   // Positions past the range read the last one; their scores are -inf.
-  uint4 kr[NG][NP], vr[8];
+  uint4 kr[NG][NP], vr[NV];
   const auto load_k = [&](int p0) __attribute__((always_inline)) {
 #pragma unroll
     for (int a = 0; a < NG; ++a) {
@@ -131,7 +180,7 @@ __global__ __launch_bounds__(64 * W, HG >= 8 ? 1 : 2) void flowkv_chunk_kernel(c
   };
   const auto load_v = [&](int p0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < NV; ++j)
       vr[j] = load_stream(reinterpret_cast<const uint4*>(Vg + (size_t)min(p0 + P * j + rs, last) * D) + db);
   };
 
@@ -145,65 +194,65 @@ __global__ __launch_bounds__(64 * W, HG >= 8 ? 1 : 2) void flowkv_chunk_kernel(c
   load_k(0);
   load_v(0);
   if constexpr (!kQRegs) {
-    for (int e = tid; e < HG * D / 2; e += 64 * W)
-      qs[e / (D / 2)][e % (D / 2)] = reinterpret_cast<const uint32_t*>(q + (size_t)(g * HG + e / (D / 2)) * D)[e % (D / 2)];
+    for (int e = tid; e < HG * D / 8; e += 64 * W)
+      reinterpret_cast<uint4*>(&qs[0][0])[e] = reinterpret_cast<const uint4*>(q + (size_t)g * HG * D)[e];
     __syncthreads();
   }
 
-  float m[HG], l[HG], y[HG][8];  // running state; l over the lane's own positions, y over its own rows
+  const int hu = u & (HG - 1);                             // the lane's head
+  const int pu = 8 * ((u >> kHBits) & ((1 << kSplit) - 1)) + kw;  // and its positions: pu + 8 (a << kSplit)
+  float m = -INFINITY, l = 0.0f;            // running state of the lane's head, l over the lane's own positions
+  float y[HG][8];                           // every head, over the lane's own rows
 #pragma unroll
-  for (int h = 0; h < HG; ++h) {
-    m[h] = -INFINITY;
-    l[h] = 0.0f;
+  for (int h = 0; h < HG; ++h)
 #pragma unroll
     for (int e = 0; e < 8; ++e) y[h][e] = 0.0f;
-  }
   for (int p0 = 0; p0 < n; p0 += SP) {
     // Scores (Eq. 6).
-    float s[HG][NG];
-#pragma unroll
-    for (int a = 0; a < NG; ++a)
-#pragma unroll
-      for (int h = 0; h < HG; ++h) {
-        float v = 0.0f;
-#pragma unroll
-        for (int i = 0; i < NP; ++i) {
-          uint4 qv;
-          if constexpr (kQRegs) qv = qr[h][i];
-          else qv = *reinterpret_cast<const uint4*>(&qs[h][32 * i + 4 * u]);
-          v = dot2(kr[a][i].x, qv.x, v);
-          v = dot2(kr[a][i].y, qv.y, v);
-          v = dot2(kr[a][i].z, qv.z, v);
-          v = dot2(kr[a][i].w, qv.w, v);
-        }
-        v += xor_lane<1>(v);
-        v += xor_lane<2>(v);
-        v += xor_lane<4>(v);
-        s[h][a] = p0 + 8 * a + kw < n ? v * scale : -INFINITY;
-      }
-    if (p0 + SP < n) load_k(p0 + SP);
-    // Running maximum (Eq. 7), exponentials (Eq. 8), correction (Eq. 9, 10).
+    float v[HG][NG];
 #pragma unroll
     for (int h = 0; h < HG; ++h) {
-      float mx = s[h][0];
 #pragma unroll
-      for (int a = 1; a < NG; ++a) mx = fmaxf(mx, s[h][a]);
-      mx = fmaxf(mx, xor_lane<8>(mx));
-      mx = fmaxf(mx, xor_lane<16>(mx));
-      mx = fmaxf(mx, xor_lane<32>(mx));
-      mx = fmaxf(mx, m[h]);
-      const float base = mx == -INFINITY ? 0.0f : mx;  // no finite score yet: exp(-inf) = 0
-      const float corr = expf(m[h] - base);
-      m[h] = mx;
-      l[h] *= corr;
+      for (int a = 0; a < NG; ++a) v[h][a] = 0.0f;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) y[h][e] *= corr;
+      for (int i = 0; i < NP; ++i) {
+        uint4 qv;
+        if constexpr (kQRegs) qv = qr[h][i];
+        else qv = *reinterpret_cast<const uint4*>(&qs[h][32 * i + 4 * u]);
 #pragma unroll
-      for (int a = 0; a < NG; ++a) {
-        const float f = expf(s[h][a] - base);
-        l[h] += f;
-        if (u == 0) fs[wave][8 * a + kw][h] = f;
+        for (int a = 0; a < NG; ++a) {
+          v[h][a] = dot2(kr[a][i].x, qv.x, v[h][a]);
+          v[h][a] = dot2(kr[a][i].y, qv.y, v[h][a]);
+          v[h][a] = dot2(kr[a][i].z, qv.z, v[h][a]);
+          v[h][a] = dot2(kr[a][i].w, qv.w, v[h][a]);
+        }
       }
+    }
+    float s[NR];
+    scatter_sum<1, HG, NG, NR>(&v[0][0], s, u);
+    if (p0 + SP < n) load_k(p0 + SP);
+    // Running maximum (Eq. 7), exponentials (Eq. 8), correction (Eq. 9, 10).
+    float mx = m;
+#pragma unroll
+    for (int a = 0; a < NR; ++a) {
+      s[a] = p0 + pu + 8 * (a << kSplit) < n ? s[a] * scale : -INFINITY;
+      mx = fmaxf(mx, s[a]);
+    }
+    if constexpr (kSplit > 0) mx = fmaxf(mx, xor_lane<(1 << kHBits)>(mx));
+    if constexpr (kSplit > 1) mx = fmaxf(mx, xor_lane<(2 << kHBits)>(mx));
+    mx = fmaxf(mx, xor_lane<8>(mx));
+    mx = fmaxf(mx, xor_lane<16>(mx));
+    mx = fmaxf(mx, xor_lane<32>(mx));
+    const float base = mx == -INFINITY ? 0.0f : mx;  // no finite score yet: exp(-inf) = 0
+    const float corr = expf(m - base);
+    m = mx;
+    l *= corr;
+    if (HG > 1 && lane < HG) cs[wave][lane] = corr;
+#pragma unroll
+    for (int a = 0; a < NR; ++a) {
+      const float f = expf(s[a] - base);
+      l += f;
+      fs[wave][pu + 8 * (a << kSplit)][hu] = f;
     }
     // (A wave's LDS instructions are carried out in order; the fences keep the
     // compiler from moving the accesses across.)
@@ -212,32 +261,39 @@ __global__ __launch_bounds__(64 * W, HG >= 8 ? 1 : 2) void flowkv_chunk_kernel(c
     // times an infinity would be NaN.
     if (p0 + SP > n) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
+      for (int j = 0; j < NV; ++j)
         if (p0 + P * j + rs >= n) vr[j] = make_uint4(0, 0, 0, 0);
     }
     // Weighted values (Eq. 11).
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int h = 0; h < HG; ++h) {
+      const float ch = HG > 1 ? cs[wave][h] : corr;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[h][e] *= ch;
+    }
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
       const float* f = fs[wave][P * j + rs];
-      const float v[8] = {bf16lo(vr[j].x), bf16hi(vr[j].x), bf16lo(vr[j].y), bf16hi(vr[j].y),
+      const float w[8] = {bf16lo(vr[j].x), bf16hi(vr[j].x), bf16lo(vr[j].y), bf16hi(vr[j].y),
                           bf16lo(vr[j].z), bf16hi(vr[j].z), bf16lo(vr[j].w), bf16hi(vr[j].w)};
 #pragma unroll
       for (int h = 0; h < HG; ++h)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) y[h][e] = fmaf(f[h], v[e], y[h][e]);
+        for (int e = 0; e < 8; ++e) y[h][e] = fmaf(f[h], w[e], y[h][e]);
     }
     if (p0 + SP < n) load_v(p0 + SP);
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   }
 
-  // Sum over the lanes: l over the positions (lanes kw), y over the rows of a
-  // load (lanes rs).
+  // Sum over the lanes: l over the lanes of a head (those that share out its
+  // positions), y over the rows of a load (lanes rs).
+  if constexpr (kSplit > 0) l += xor_lane<(1 << kHBits)>(l);
+  if constexpr (kSplit > 1) l += xor_lane<(2 << kHBits)>(l);
+  l = sum_lanes_from<8>(l);
 #pragma unroll
-  for (int h = 0; h < HG; ++h) {
-    l[h] = sum_lanes_from<8>(l[h]);
+  for (int h = 0; h < HG; ++h)
 #pragma unroll
     for (int e = 0; e < 8; ++e) y[h][e] = sum_lanes_from<R>(y[h][e]);
-  }
   if constexpr (W == 1) {
 #pragma unroll
     for (int h = 0; h < HG; ++h) {
@@ -246,10 +302,11 @@ __global__ __launch_bounds__(64 * W, HG >= 8 ? 1 : 2) void flowkv_chunk_kernel(c
         reinterpret_cast<float4*>(part + 4 + 8 * db)[0] = make_float4(y[h][0], y[h][1], y[h][2], y[h][3]);
         reinterpret_cast<float4*>(part + 4 + 8 * db)[1] = make_float4(y[h][4], y[h][5], y[h][6], y[h][7]);
       }
-      if (lane == 0) {
-        part[0] = m[h];
-        part[1] = l[h];
-      }
+    }
+    if (lane < HG) {
+      float* part = work + ((size_t)(g * HG + lane) * nchunks + c) * kPart;
+      part[0] = m;
+      part[1] = l;
     }
   } else {
 #pragma unroll
@@ -258,10 +315,10 @@ __global__ __launch_bounds__(64 * W, HG >= 8 ? 1 : 2) void flowkv_chunk_kernel(c
         reinterpret_cast<float4*>(&ys[wave][h][8 * db])[0] = make_float4(y[h][0], y[h][1], y[h][2], y[h][3]);
         reinterpret_cast<float4*>(&ys[wave][h][8 * db])[1] = make_float4(y[h][4], y[h][5], y[h][6], y[h][7]);
       }
-      if (lane == 0) {
-        ms[wave][h] = m[h];
-        ls[wave][h] = l[h];
-      }
+    }
+    if (lane < HG) {
+      ms[wave][lane] = m;
+      ls[wave][lane] = l;
     }
     __syncthreads();
     // The waves' states merged in wave order (a wave without a finite score
@@ -377,34 +434,52 @@ __global__ __launch_bounds__(kFkvThreads) void flowkv_merge_kernel(const float* 
   }
 }
 
-// Waves per workgroup and positions per workgroup of phase 1.  Up to two
-// waves of one sub-chunk per CU: one wave and one sub-chunk each (latency is
-// the whole cost).  Beyond, four waves: the longest chunk up to 512 positions
-// that still gives every CU a workgroup, down to one sub-chunk per wave (two
-// workgroups per CU, so half the chunk and twice the partials to merge: 1-7%
-// slower over the Gemma3 stacks at 32K).
+// Waves and positions per workgroup of phase 1.  Up to two sub-chunks per CU:
+// one sub-chunk per wave, and one wave per workgroup as long as that leaves at
+// most 128 partials per head, which the merge reads in one pass wherever it
+// splits the dims 16 ways (2500 positions of one head at d = 256 as 157
+// partials 6.7 us, as 79 partials 5.9).  Beyond, four waves and as few rounds
+// of one workgroup per CU as chunks of at most 512 positions need, all chunks
+// alike: a chunk of the next power of two can leave a last round that a few
+// CUs work through alone (4 heads of one group at d = 256, 70000 positions:
+// 274 chunks of 256 positions 28.7 us, 244 of 288 19.9).  Two workgroups per
+// CU, so half the chunk and twice the partials, were 1-7% slower over the
+// Gemma3 stacks at 32K.  Past the number of partials that the static scratch
+// holds, chunks of 512 positions, so that it serves the longest ranges it can.
 struct FlowkvSplit {
   int waves, chunk;
 };
-static FlowkvSplit flowkv_split(int64_t n, int G, int d, int cus) {
-  const int sp = kSubBytes / (2 * d);
-  if (ceil_div(n, sp) * G <= 2 * cus) return {1, sp};
-  int chunk = 512;
-  while (chunk > 4 * sp && ceil_div(n, chunk) * G < cus) chunk >>= 1;
-  return {4, chunk};
+constexpr size_t kStaticScratchBytes = Q4NX_FLOWKV_STATIC_BYTES;
+static FlowkvSplit flowkv_split(int64_t n, int64_t H, int64_t G, int64_t d, int cus) {
+  const int sp = sub_positions((int)d);
+  const int64_t nsub = ceil_div(n, sp);
+  if (nsub * G <= 2 * cus) {
+    const int waves = nsub <= 128 ? 1 : nsub <= 256 ? 2 : 4;
+    return {waves, waves * sp};
+  }
+  for (int64_t r = std::max<int64_t>(1, n * G / (512 * (int64_t)cus));; ++r) {
+    const int64_t chunk = ceil_div(ceil_div(n, std::max<int64_t>(1, r * cus / G)), 4 * sp) * 4 * sp;
+    if (chunk > 512) continue;
+    const bool fits = (size_t)(H * ceil_div(n, chunk) * (d + 4)) * sizeof(float) <= kStaticScratchBytes;
+    return {4, fits ? (int)chunk : 512};
+  }
 }
 
 template <int D, int HG>
 static void launch_flowkv(const uint16_t* q, const uint16_t* K, const uint16_t* V, int64_t L, int G, int j0, int j1,
                           float scale, float* work, void* out, int out_bf16, hipStream_t stream, int cus) {
-  const FlowkvSplit sp = flowkv_split(j1 - j0, G, D, cus);
+  const FlowkvSplit sp = flowkv_split(j1 - j0, G * HG, G, D, cus);
   const int nchunks = (int)ceil_div(j1 - j0, sp.chunk);
-  if (sp.waves == 1)
-    hipLaunchKernelGGL((flowkv_chunk_kernel<1, D, HG>), dim3(nchunks, G), dim3(64), 0, stream, q, K, V, L, j0, j1,
+  const auto chunks = [&](auto wc) {
+    constexpr int W = decltype(wc)::value;
+    hipLaunchKernelGGL((flowkv_chunk_kernel<W, D, HG>), dim3(nchunks, G), dim3(64 * W), 0, stream, q, K, V, L, j0, j1,
                        sp.chunk, scale, work);
-  else
-    hipLaunchKernelGGL((flowkv_chunk_kernel<4, D, HG>), dim3(nchunks, G), dim3(256), 0, stream, q, K, V, L, j0, j1,
-                       sp.chunk, scale, work);
+  };
+  switch (sp.waves) {
+    case 1: chunks(std::integral_constant<int, 1>{}); break;
+    case 2: chunks(std::integral_constant<int, 2>{}); break;
+    default: chunks(std::integral_constant<int, 4>{}); break;
+  }
   // Dims per merge workgroup: halved (down to 16) until there are at least
   // 128 workgroups.
   const int H = G * HG;
@@ -455,7 +530,6 @@ static bool dispatch_hg(int hg, const uint16_t* q, const uint16_t* K, const uint
 // kernel (on the host it is only a stand-in for the symbol): the device
 // address comes from hipGetSymbolAddress, taken once per device with that
 // device current.
-constexpr size_t kStaticScratchBytes = Q4NX_FLOWKV_STATIC_BYTES;
 static __device__ __align__(256) float scratch[kStaticScratchBytes / sizeof(float)];
 
 static q4nx_status static_scratch(float** out) {
@@ -503,7 +577,7 @@ static q4nx_status flowkv_entry(const uint16_t* d_q, const uint16_t* d_k, const 
     return fail(Q4NX_ERR_BUFFER_TOO_SMALL, f + ": workspace smaller than q4nx_flowkv_workspace_size");
   const int cus = current_device_cus();
   if (!work) {
-    const size_t need = (size_t)H * (size_t)ceil_div(j1 - j0, flowkv_split(j1 - j0, (int)G, (int)d, cus).chunk) *
+    const size_t need = (size_t)H * (size_t)ceil_div(j1 - j0, flowkv_split(j1 - j0, H, G, d, cus).chunk) *
                         (size_t)(d + 4) * sizeof(float);
     if (need > kStaticScratchBytes)
       return fail(Q4NX_ERR_BUFFER_TOO_SMALL, f + ": the chunk partials (" + std::to_string(need) +

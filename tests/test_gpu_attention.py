@@ -114,14 +114,17 @@ def test_flowkv_bf16_output_and_repeatable(q4):
 
 
 # The edges of phase 1's split: one wave per workgroup with one, a whole and a
-# ragged sub-chunk (16, 32 and 64 positions for d = 256, 128 and 64), the last
-# shape that takes it and the first that takes four waves (n G = 512 sub-chunks
-# and one more position), four waves with empty ones in the last chunk, and
-# eight query heads per group (the query in LDS) at every d.
+# ragged sub-chunk (16 positions for d = 256 and 128, 32 for 64), the last
+# shapes of one, two and four such waves per workgroup (128, 256 and 512
+# sub-chunks) and the first of the next kind, chunks of even rounds (waves with
+# no position in the last chunk, one position in the last chunk, more than one
+# round), and every number of query heads per group at every d.
 @pytest.mark.parametrize("H,G,d,n", [(8, 4, 256, 16), (8, 4, 256, 17), (32, 16, 128, 31), (8, 8, 64, 65),
                                      (8, 4, 256, 2048), (8, 4, 256, 2049), (16, 16, 128, 1024), (16, 16, 128, 1025),
                                      (4, 1, 256, 8193), (8, 1, 256, 900), (8, 1, 128, 20000), (64, 8, 256, 4100),
-                                     (64, 8, 64, 4100)])
+                                     (64, 8, 64, 4100), (4, 1, 256, 2049), (4, 1, 256, 4097), (8, 1, 256, 4096),
+                                     (2, 1, 128, 4000), (1, 1, 64, 8200), (4, 1, 64, 4097), (2, 1, 64, 33),
+                                     (16, 8, 256, 9000), (16, 16, 128, 16385), (4, 1, 128, 70000), (2, 2, 64, 140001)])
 def test_flowkv_split_edges(q4, H, G, d, n):
     print("[case] flowkv split", H, G, d, n, flush=True)
     q, K, V = _case(H, G, d, n + 3, seed=n)
@@ -152,3 +155,23 @@ def test_flowkv_infinite_last_value(q4, H, G, d, n):
     ref, bound = decode_attention(q, K, V, n - 1, 0, scale)
     rest = np.delete(np.arange(d), [3, 5])
     assert (np.abs(got - ref)[:, rest] <= 2e-3 * bound[:, rest] + 1e-6).all()
+
+
+@pytest.mark.parametrize("H,G,d,n", [(8, 1, 256, 2016 * 512), (64, 16, 128, 496 * 512)])
+def test_flowkv_static_serves_its_longest_ranges(q4, H, G, d, n):
+    """The static scratch holds as many chunks of 512 positions as its 16 MiB
+    allow (2016 of 8 heads at d = 256): such a range, where shorter chunks
+    would not fit, is accepted, with the bits of the workspace call."""
+    print("[case] flowkv static limit", H, G, d, n, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q = torch.randn(H, d, device="cuda", generator=g).bfloat16()
+    K = torch.randn(G, n, d, device="cuda", generator=g, dtype=torch.bfloat16)
+    V = torch.randn(G, n, d, device="cuda", generator=g, dtype=torch.bfloat16)
+    work = torch.empty(q4.q4nx_flowkv_workspace_size(H, d, n) // 4, dtype=torch.float32, device="cuda")
+    o = [torch.full((H, d), float("nan"), device="cuda") for _ in range(2)]
+    q4.q4nx_flowkv_decode(q, K, V, H, G, d, n, n - 1, 0, 0.05, o[0], work)
+    q4.q4nx_flowkv_decode_static(q, K, V, H, G, d, n, n - 1, 0, 0.05, o[1])
+    torch.cuda.synchronize()
+    assert torch.isfinite(o[0]).all() and torch.equal(o[0].view(torch.int32), o[1].view(torch.int32))
+    p = torch.softmax(0.05 * (K[0].float() @ q[:H // G].float().T), dim=0)      # group 0, float32
+    assert torch.allclose(p.T @ V[0].float(), o[0][:H // G], rtol=0, atol=1e-3)
