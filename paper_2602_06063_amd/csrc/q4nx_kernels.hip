@@ -316,14 +316,19 @@ __device__ __forceinline__ void load_groups(const float* __restrict__ W, int64_t
 // beyond 16 the code is 15 or 0 with room to spare); a level RN(d q + m) is
 // off by at most u (15 + R).  e = u (128 + R) leaves a factor of about two on
 // the first.  A lane with a t that close to a half-integer (one group in two
-// thousand for weights around zero) compares the two levels around it: up to
-// R = kQuantMaxR, e is below 1/100 and the levels are distinct.  A group with
-// a NaN, a value to be clamped or a larger R takes the exact search, in a loop
-// over the LDS slot (unrolled, it held 232 registers and halved the rate of
-// the whole kernel).
+// thousand for weights around zero) compares the two levels around the t it
+// has: up to R = kQuantMaxR = 2^22, e is at most about 1/4, so the nearest
+// level is one of the two, and d is more than an ulp of any level, so the
+// levels are distinct.  A group with a NaN or a value to be clamped is taken
+// into the domain and goes through once more.  A larger R (32 weights within
+// a few ulps of each other) takes the exact search, eight weights at a time
+// from the LDS slot (all 32 unrolled, it held 232 registers and halved the
+// rate of the whole kernel).
 // The exact search for every weight (35 operations) was bound by the VALU:
-// 21504 x 5376 in 155 us; this takes 85 us (6.3 TB/s).
-constexpr float kQuantMaxR = 131072.0f, kQuantU = 5.9604644775390625e-08f;
+// 21504 x 5376 in 130-158 us; this takes 87 us (6.1 TB/s), 90 with every R
+// above 2^17, 94 with a NaN in every group (250 us where those took the exact
+// search, one weight at a time), and 200 us with every R above 2^22.
+constexpr float kQuantMaxR = 4194304.0f, kQuantU = 5.9604644775390625e-08f;
 
 __global__ __launch_bounds__(256) void quantize_kernel(const float* __restrict__ W, int64_t N, int64_t K, int64_t KB,
                                                        int64_t nblocks, uint8_t* __restrict__ blob) {
@@ -338,44 +343,59 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float* __restrict__
     float w[32];
     load_groups(W, N, K, i * kBlockRows + 8 * t, j * kBlockCols, lane, slots[t], w);
     if (i * kBlockRows + r < N && j * kBlockCols + kGroup * c < K) {
-      float lo = w[0], hi = w[0];  // (a NaN shows up below)
+      bool search;
+#pragma unroll 1
+      for (;;) {
+        float lo = w[0], hi = w[0];
 #pragma unroll
-      for (int e = 1; e < 32; ++e) {
-        lo = fminf(lo, w[e]);
-        hi = fmaxf(hi, w[e]);
-      }
-      lo = lo + 0.0f;  // a zero minimum is +0
-      sb = bf16_rne_flushed((hi - lo) / 15.0f);
-      mb = bf16_rne_flushed(lo);
-      const float d = bf16_to_f32(sb), m = bf16_to_f32(mb);
-      const float inv = d == 0.0f ? 0.0f : __builtin_amdgcn_rcpf(d);  // d = 0: every code is 0
-      const float R = fabsf(m) * inv, near = 0.5f - kQuantU * (128.0f + R);
-      bool search = !(lo >= -kQuantClamp && hi <= kQuantClamp && R <= kQuantMaxR);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        uint32_t ev = 0, od = 0;  // codes of the even and odd columns, a byte each
-        bool sure = true;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float x = (w[8 * u + e] - m) * inv;
-          const float q = rintf(x);
-          sure &= fabsf(x - q) <= near;  // false for a NaN
-          uint32_t& dst = (e & 1) ? od : ev;
-          dst = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(q, 0.0f, 15.0f), e >> 1, dst);
+        for (int e = 1; e < 32; ++e) {
+          lo = fminf(lo, w[e]);
+          hi = fmaxf(hi, w[e]);
         }
-        if (!sure) {
-          ev = od = 0;
+        lo = lo + 0.0f;  // a zero minimum is +0
+        sb = bf16_rne_flushed((hi - lo) / 15.0f);
+        mb = bf16_rne_flushed(lo);
+        const float d = bf16_to_f32(sb), m = bf16_to_f32(mb);
+        const float inv = d == 0.0f ? 0.0f : __builtin_amdgcn_rcpf(d);  // d = 0: every code is 0
+        const float R = fabsf(m) * inv, near = 0.5f - kQuantU * (128.0f + R);
+        bool outside = !(lo >= -kQuantClamp && hi <= kQuantClamp);  // (a NaN shows up below)
+        search = !(R <= kQuantMaxR);
+        if (__builtin_expect(__ballot(!search) == 0, 0)) {  // the whole wave: no codes to be had here
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float v = w[8 * u + e];
-            search |= v != v;
-            const float q = __builtin_amdgcn_fmed3f(floorf((v - m) * inv), 0.0f, 14.0f);
-            const double below = (double)v - (double)fmaf(q, d, m), above = (double)fmaf(q + 1.0f, d, m) - (double)v;
-            uint32_t& dst = (e & 1) ? od : ev;
-            dst = __builtin_amdgcn_cvt_pk_u8_f32(above < below ? q + 1.0f : q, e >> 1, dst);
+          for (int e = 0; e < 32; ++e) outside |= w[e] != w[e];
+        } else {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            uint32_t ev = 0, od = 0;  // codes of the even and odd columns, a byte each
+            bool sure = true;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const float x = (w[8 * u + e] - m) * inv;
+              const float q = rintf(x);
+              sure &= fabsf(x - q) <= near;  // false for a NaN
+              uint32_t& dst = (e & 1) ? od : ev;
+              dst = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(q, 0.0f, 15.0f), e >> 1, dst);
+            }
+            if (!sure) {
+              ev = od = 0;
+#pragma unroll
+              for (int e = 0; e < 8; ++e) {
+                const float v = w[8 * u + e];
+                outside |= v != v;
+                const float q = __builtin_amdgcn_fmed3f(floorf((v - m) * inv), 0.0f, 14.0f);
+                const double below = (double)v - (double)fmaf(q, d, m), above = (double)fmaf(q + 1.0f, d, m) - (double)v;
+                uint32_t& dst = (e & 1) ? od : ev;
+                dst = __builtin_amdgcn_cvt_pk_u8_f32(above < below ? q + 1.0f : q, e >> 1, dst);
+              }
+            }
+            codes[u] = ev | (od << 4);
           }
         }
-        codes[u] = ev | (od << 4);
+        if (!outside) break;
+        // Into the domain, and once more.
+#pragma unroll
+        for (int e = 0; e < 32; ++e)
+          w[e] = w[e] != w[e] ? 0.0f : __builtin_amdgcn_fmed3f(w[e], -kQuantClamp, kQuantClamp);
       }
       if (search) {
         const float* g = reinterpret_cast<const float*>(slots[t] + lane * kQuantGroupBytes);
@@ -383,29 +403,16 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float* __restrict__
           const float x = g[e];
           return x != x ? 0.0f : fminf(fmaxf(x, -kQuantClamp), kQuantClamp);
         };
-        lo = kQuantClamp;
-        hi = -kQuantClamp;
-#pragma unroll 1
-        for (int e = 0; e < 32; ++e) {
-          const float x = clamped(e);
-          lo = fminf(lo, x);
-          hi = fmaxf(hi, x);
-        }
-        lo = lo + 0.0f;
-        sb = bf16_rne_flushed((hi - lo) / 15.0f);
-        mb = bf16_rne_flushed(lo);
         const float de = bf16_to_f32(sb), me = bf16_to_f32(mb);
-        uint32_t word = 0;
 #pragma unroll 1
-        for (int e = 0; e < 32; ++e) {
-          word |= (uint32_t)quant_code(clamped(e), de, me) << (4 * (e & 7));
-          if ((e & 7) == 7) {
-            codes[0] = e == 7 ? word : codes[0];
-            codes[1] = e == 15 ? word : codes[1];
-            codes[2] = e == 23 ? word : codes[2];
-            codes[3] = e == 31 ? word : codes[3];
-            word = 0;
-          }
+        for (int u = 0; u < 4; ++u) {
+          uint32_t word = 0;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) word |= (uint32_t)quant_code(clamped(8 * u + e), de, me) << (4 * e);
+          codes[0] = u == 0 ? word : codes[0];
+          codes[1] = u == 1 ? word : codes[1];
+          codes[2] = u == 2 ? word : codes[2];
+          codes[3] = u == 3 ? word : codes[3];
         }
       }
     }

@@ -466,6 +466,28 @@ def test_quantize_near_ties_bit_exact(q4, seed):
     assert np.array_equal(blob.cpu().numpy(), oracle.pack(*oracle.quantize(W)))
 
 
+@pytest.mark.parametrize("share", [1.0, 0.02])
+def test_quantize_out_of_domain_groups_bit_exact(q4, share):
+    """Groups with a NaN, an infinity or a magnitude above 2^100, all of them
+    or one in fifty (a lane in every other wave), around offsets of every size
+    against the scale: taken into the domain and quantized like any other."""
+    N, K = 67, 1056
+    _say("quantize out of domain", share)
+    rng = np.random.default_rng(int(100 * share))
+    G = K // 32
+    m = np.exp2(rng.uniform(-3, 26, (N, G, 1))) * rng.choice([-1.0, 1.0], (N, G, 1))
+    W = (m + rng.uniform(0, 15, (N, G, 32))).astype(np.float32)
+    bad = np.array([np.nan, np.inf, -np.inf, 2e30, -2e30, np.nan], np.float32)
+    hit = rng.random((N, G)) < share
+    W[hit, rng.integers(0, 32, hit.sum())] = rng.choice(bad, hit.sum())
+    W[0, 0] = np.nan
+    W = np.ascontiguousarray(W.reshape(N, K))
+    blob = torch.full((q4.q4nx_packed_size(N, K),), 0xAB, dtype=torch.uint8, device="cuda")
+    q4.q4nx_quantize(torch.from_numpy(W).cuda(), N, K, blob)
+    torch.cuda.synchronize()
+    assert np.array_equal(blob.cpu().numpy(), oracle.pack(*oracle.quantize(W)))
+
+
 # ----------------------------------------------------------------- measurement aid
 def test_stream_read_folds_every_word(q4):
     """q4nx_stream_read reads every 16-byte piece exactly once: its per-wave
