@@ -41,3 +41,11 @@ inline bool aligned(const void* p, size_t a) {
 }
 
 }  // namespace q4nx
+
+// Not part of the ABI, for tests: the kernels that a matrix product runs on
+// the current device (256 CUs without one), in launch order, as text in
+// text[size]: "ks 80x64", "tile 256x192 + tile 128x128", "dequant + gemm256
+// 256x256", "split4 256x256", "general 128x64".  w_format as q4nx_gemm_ex;
+// have_work: whether the call has a workspace.  Returns the length, or -1.
+extern "C" int q4nx_internal_gemm_launches(int w_format, int64_t M, int64_t N, int64_t K, int have_work, char* text,
+                                           int size);

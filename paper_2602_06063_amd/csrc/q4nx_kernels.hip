@@ -1972,7 +1972,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_kernel(
 // outputs, and products of many columns take one round of tiles where 64 columns
 // needed two.  4B gate/up at 77 rows 31.1 -> 21.5 us, 27B gate/up at 77 rows 96
 // -> 77, 27B o at 300 rows 31.8 -> 29.7 (MXFP4 28.0 -> 25.3).  (128 columns
-// spill or were slower.)
+// spill or were slower.)  bf16 weights run the same tiles, X in two passes where
+// the LDS does not hold both operands' rows, and one unit of W ahead where the
+// registers do not hold two: as 64 x 64 tiles instead, and the smaller ones
+// spilling at two waves per SIMD, 77 x 20480 x 2560 took 47.6 us (now 29.4),
+// 223 x 5376 x 4096 41.7 (26.7), 226 x 2560 x 10240 94.8 (40.5).
 // The order of every sum is fixed by M, N and K, and is the same for the three
 // weight operands, so they agree bit for bit on the same bf16 weights.
 constexpr int kKsUnit = 128;              // columns of K per unit
@@ -1991,18 +1995,27 @@ struct KsUnit<NT, kWBf16> {
   u32x4 q[4 * NT];
 };
 
+// Blocks of 16 rows of X staged at a time.  The LDS holds nine blocks of bf16
+// rows per wave, so beside NT blocks of bf16 W the X of the larger tiles goes
+// through in passes (each output still takes its products in the same order).
+template <int MT, int NT, int WF>
+constexpr int ks_x_blocks() {
+  if (WF != kWBf16) return MT;
+  const int passes = (MT + 8 - NT) / (9 - NT);
+  return (MT + passes - 1) / passes;
+}
 template <int MT, int NT, int WF>
 constexpr int ks_wave_lds() {
-  return 16 * MT * kKsRow + 16 * NT * (WF == kWBf16 ? kKsRow : kKsCodeRow);
+  return 16 * ks_x_blocks<MT, NT, WF>() * kKsRow + 16 * NT * (WF == kWBf16 ? kKsRow : kKsCodeRow);
 }
 template <int MT, int NT, int W, int WF>
 constexpr int ks_lds_bytes() {
   return W * std::max(ks_wave_lds<MT, NT, WF>(), MT * NT * 1024);
 }
 
-// Tiles of 16 and more blocks take the whole register file (one wave per SIMD).
+// A tile of which the LDS holds one takes the whole register file (one wave per SIMD).
 template <int MT, int NT, int W, int WF>
-__global__ __launch_bounds__(64 * W, MT * NT >= 16 || MT > 4 ? 1 : 2) void gemm_ks_kernel(
+__global__ __launch_bounds__(64 * W, (ks_lds_bytes<MT, NT, W, WF>() > 80 * 1024 ? 1 : 2)) void gemm_ks_kernel(
     const uint16_t* __restrict__ X, const uint8_t* __restrict__ wsrc, void* __restrict__ Y, int M, int N, int K,
     int ldy, int KB, int NS, int tiles_n, int y_bf16) {
   constexpr int kBB = wblock_bytes<WF>();
@@ -2017,7 +2030,8 @@ __global__ __launch_bounds__(64 * W, MT * NT >= 16 || MT > 4 ? 1 : 2) void gemm_
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, h = lane >> 4;
   uint8_t* const xs = reinterpret_cast<uint8_t*>(gl) + wave * ks_wave_lds<MT, NT, WF>();
-  uint8_t* const ws = xs + 16 * MT * kKsRow;
+  constexpr int kXB = ks_x_blocks<MT, NT, WF>();
+  uint8_t* const ws = xs + 16 * kXB * kKsRow;
 
   const int rows_x = min(16 * MT, M - m0);
   const __amdgpu_buffer_rsrc_t rsx = __builtin_amdgcn_make_buffer_rsrc(
@@ -2060,13 +2074,14 @@ __global__ __launch_bounds__(64 * W, MT * NT >= 16 || MT > 4 ? 1 : 2) void gemm_
 
   // Loads of the wave's i-th unit.  Columns past K, and units past the wave's
   // last, read 0 (with the scalar offset inside the descriptor).
-  auto load_x = [&](u32x4 (&R)[kXI], int i) {
+  // (X: registers j0 .. j1 - 1.)
+  auto load_x = [&](u32x4 (&R)[kXI], int i, int j0, int j1) {
     const int k0 = (wave + W * i) * kKsUnit;
     const bool on = i < nu;  // uniform over the wave
     const uint32_t past = on && k0 + 8 * c < K ? 0 : kPastEnd;
     const int so = on ? 2 * k0 : 0;
 #pragma unroll
-    for (int j = 0; j < kXI; ++j)
+    for (int j = j0; j < j1; ++j)
       R[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsx, vx[j] | past, so, 0));
   };
   auto load_w = [&](KsUnit<NT, WF>& R, int i) {
@@ -2101,16 +2116,18 @@ __global__ __launch_bounds__(64 * W, MT * NT >= 16 || MT > 4 ? 1 : 2) void gemm_
 #pragma unroll
     for (int b = 0; b < NT; ++b) acc[a][b] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
 
+  // Two units of W ahead; one where two bf16 ones do not fit the registers.
+  constexpr int kAhead = WF == kWBf16 && MT * NT >= 30 ? 1 : 2;
   u32x4 Xr[kXI];
   KsUnit<NT, WF> W0, W1;
   load_w(W0, 0);
-  load_x(Xr, 0);
-  load_w(W1, 1);
+  load_x(Xr, 0, 0, kXI);
+  if constexpr (kAhead == 2) load_w(W1, 1);
   // One unit: its X and W registers go to LDS and are reloaded at once, then
   // the MFMAs from LDS.
   auto unit = [&](KsUnit<NT, WF>& Wr, int i) {
 #pragma unroll
-    for (int j = 0; j < kXI; ++j) *reinterpret_cast<u32x4*>(xs + (h + 4 * j) * kKsRow + 16 * c) = Xr[j];
+    for (int j = 0; j < 4 * kXB; ++j) *reinterpret_cast<u32x4*>(xs + (h + 4 * j) * kKsRow + 16 * c) = Xr[j];
     float d[NT], mo[NT];
     if constexpr (WF == kWBf16) {
 #pragma unroll
@@ -2131,8 +2148,8 @@ __global__ __launch_bounds__(64 * W, MT * NT >= 16 || MT > 4 ? 1 : 2) void gemm_
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_sched_barrier(0);
-    load_x(Xr, i + 1);
-    load_w(Wr, i + 2);
+    load_x(Xr, i + 1, 0, 4 * kXB);
+    load_w(Wr, i + kAhead);
     u32x4 q[NT];
     if constexpr (WF != kWBf16) {
 #pragma unroll
@@ -2140,9 +2157,9 @@ __global__ __launch_bounds__(64 * W, MT * NT >= 16 || MT > 4 ? 1 : 2) void gemm_
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      bf16x8 A[MT];
+      bf16x8 A[kXB];
 #pragma unroll
-      for (int a = 0; a < MT; ++a)
+      for (int a = 0; a < kXB; ++a)
         A[a] = *reinterpret_cast<const bf16x8*>(xs + (16 * a + c) * kKsRow + 64 * h + 16 * u);
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
@@ -2151,18 +2168,47 @@ __global__ __launch_bounds__(64 * W, MT * NT >= 16 || MT > 4 ? 1 : 2) void gemm_
         else if constexpr (WF == kWMX) b = mx8_bf16(q[t][u], d[t]);
         else b = *reinterpret_cast<const u32x4*>(ws + (16 * t + c) * kKsRow + 64 * h + 16 * u);
 #pragma unroll
-        for (int a = 0; a < MT; ++a)
+        for (int a = 0; a < kXB; ++a)
           acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[a], __builtin_bit_cast(bf16x8, b), acc[a][t], 0, 0, 0);
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    if constexpr (kXB < MT) {  // bf16 W: the other rows of X
+      static_assert(MT <= 2 * kXB, "two passes");
+      constexpr int kRest = MT - kXB;
+#pragma unroll
+      for (int j = 0; j < 4 * kRest; ++j)
+        *reinterpret_cast<u32x4*>(xs + (h + 4 * j) * kKsRow + 16 * c) = Xr[4 * kXB + j];
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_sched_barrier(0);
+      load_x(Xr, i + 1, 4 * kXB, kXI);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        bf16x8 A[kRest];
+#pragma unroll
+        for (int a = 0; a < kRest; ++a)
+          A[a] = *reinterpret_cast<const bf16x8*>(xs + (16 * a + c) * kKsRow + 64 * h + 16 * u);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const bf16x8 b = *reinterpret_cast<const bf16x8*>(ws + (16 * t + c) * kKsRow + 64 * h + 16 * u);
+#pragma unroll
+          for (int a = 0; a < kRest; ++a)
+            acc[kXB + a][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[a], b, acc[kXB + a][t], 0, 0, 0);
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    }
   };
   int i = 0;
-  for (; i + 1 < nu; i += 2) {
-    unit(W0, i);
-    unit(W1, i + 1);
+  if constexpr (kAhead == 2) {
+    for (; i + 1 < nu; i += 2) {
+      unit(W0, i);
+      unit(W1, i + 1);
+    }
+    if (i < nu) unit(W0, i);
+  } else {
+    for (; i < nu; ++i) unit(W0, i);
   }
-  if (i < nu) unit(W0, i);
 
   // Add the waves' partial tiles in wave order.  Element e of lane l of block
   // (a, t) is row 16a + 4h + e, column 16t + c.
@@ -2381,18 +2427,31 @@ static double wide_us(const WideTile& t, double tiles, double K, int cus, bool d
 
 // Tiles of gemm_ks_kernel (16 mt rows x 16 nt outputs, K over `waves` waves):
 // a tile takes fixed_us + unit_us per 128-column unit on a CU, a launch
-// kKsLaunchUs more.
+// kKsLaunchUs more; with bf16 weights `bf16` times that (four times the bytes
+// of W per tile, and X staged in two passes beside the larger tiles).
 struct KsTile {
   int mt, nt, waves;
-  float fixed_us, unit_us;
+  float fixed_us, unit_us, bf16;
 };
-constexpr KsTile kKsTiles[] = {{1, 1, 8, 1.0f, 0.09f}, {1, 2, 4, 1.0f, 0.15f}, {2, 2, 4, 0.9f, 0.18f}, {3, 2, 4, 1.6f, 0.24f},
-                               {2, 4, 4, 1.8f, 0.31f}, {3, 4, 4, 3.4f, 0.36f}, {4, 4, 4, 4.4f, 0.40f}, {5, 4, 4, 4.8f, 0.50f},
-                               {6, 4, 4, 5.1f, 0.57f}, {8, 4, 4, 6.6f, 0.675f}, {4, 5, 4, 6.0f, 0.49f}, {5, 5, 4, 7.0f, 0.55f},
-                               {4, 6, 4, 6.0f, 0.58f}, {5, 6, 4, 6.5f, 0.65f}, {6, 6, 4, 7.2f, 0.70f}};
+constexpr KsTile kKsTiles[] = {
+    {1, 1, 8, 1.0f, 0.09f, 0.90f}, {1, 2, 4, 1.0f, 0.15f, 0.95f}, {2, 2, 4, 0.9f, 0.18f, 0.95f},
+    {3, 2, 4, 1.6f, 0.24f, 0.95f}, {2, 4, 4, 1.8f, 0.31f, 1.03f}, {3, 4, 4, 3.4f, 0.36f, 1.05f},
+    {4, 4, 4, 4.4f, 0.40f, 1.08f}, {5, 4, 4, 4.8f, 0.50f, 1.10f}, {6, 4, 4, 5.1f, 0.57f, 1.10f},
+    {8, 4, 4, 6.6f, 0.675f, 1.20f}, {4, 5, 4, 6.0f, 0.49f, 1.15f}, {5, 5, 4, 7.0f, 0.55f, 1.30f},
+    {4, 6, 4, 6.0f, 0.58f, 1.15f}, {5, 6, 4, 6.5f, 0.65f, 1.15f}, {6, 6, 4, 7.2f, 0.70f, 1.35f}};
 constexpr int kKsConfigs = (int)(sizeof(kKsTiles) / sizeof(kKsTiles[0]));
 constexpr double kKsLaunchUs = 3.2;
 constexpr int64_t kKsMaxTiles = 16384;  // beyond it the chip is full many times over
+// bf16 weights take about kOtherBf16 of the Q4NX times in the other launches,
+// and no launch reads them faster than kBf16ReadBytesPerUs.  The few-rows tile
+// that is the fastest for Q4NX weights runs for all operands (one order of the
+// sums) unless Q4NX and bf16 together would lose more than the tables' error.
+// Measured on MI355X, the few-rows tile against the other launches (Q4NX, bf16
+// us): refused at 705 x 2944 x 2304 (24.7 and 27.2 against 25.5 and 19.7), 261 x
+// 13309 x 2208 (46 and 56 against 38 and 38) and 391 x 12099 x 6560 (116 and
+// 141 against 112 and 102); taken at 303 x 5419 x 4096 (29.8 and 36.6 against
+// 31.5 and 31.1) and 77 x 20480 x 2560 (21.3 and 29.4 against 28.2 and 33.1).
+constexpr double kOtherBf16 = 0.8, kBf16ReadBytesPerUs = 4.0e6, kKsMaxLoss = 1.18;
 
 // What a full round of the plan's tiles (kGemmTiles) takes: those the general
 // kernel still computes (K with a tail, or past the wide kernels' range) and
@@ -2470,9 +2529,10 @@ static double plan_us(const GemmRegion* plan, int count, int64_t K, int cus) {
   return us;
 }
 
-// The fastest gemm_ks_kernel tile for a product that takes `best` us
-// otherwise, or -1 if none is faster.
-static int ks_choose(int64_t M, int64_t N, int64_t K, int cus, double best) {
+// The fastest gemm_ks_kernel tile for a product that takes `other` us
+// otherwise, or -1 if none is faster or bf16 weights lose too much.
+static int ks_choose(int64_t M, int64_t N, int64_t K, int cus, double other) {
+  double best = other;
   int pick = -1;
   const double units = (double)ceil_div(K, kKsUnit);
   for (int i = 0; i < kKsConfigs; ++i) {
@@ -2491,6 +2551,10 @@ static int ks_choose(int64_t M, int64_t N, int64_t K, int cus, double best) {
       pick = i;
     }
   }
+  if (pick < 0) return -1;
+  const double read = 2.0 * (double)N * (double)K / kBf16ReadBytesPerUs;
+  const double bf16 = std::max(kKsTiles[pick].bf16 * best, read), other_bf16 = std::max(kOtherBf16 * other, read);
+  if (best + bf16 > kKsMaxLoss * (other + other_bf16)) return -1;
   return pick;
 }
 
@@ -2638,30 +2702,14 @@ static q4nx_status launch_ks(int64_t M, int64_t N, int64_t K, const uint16_t* X,
   return Q4NX_OK;
 }
 
-// The product by gemm_ks_kernel with tile `cfg` of kKsTiles.  bf16 weights
-// take more LDS per unit: their tiles stop at 64 x 64 (the same waves and
-// units, hence the same bits).
-template <int WF>
+// The product by gemm_ks_kernel with tile `cfg` of kKsTiles (the same for every operand).
+template <int WF, int I = 0>
 static q4nx_status launch_ks_config(int cfg, int64_t M, int64_t N, int64_t K, const uint16_t* X, const void* w,
                                     void* Y, int y_bf16, hipStream_t stream) {
-  constexpr bool big = WF != kWBf16;
-  switch (cfg) {
-    case 0: return launch_ks<1, 1, 8, WF>(M, N, K, X, w, Y, y_bf16, stream);
-    case 1: return launch_ks<1, 2, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
-    case 2: return launch_ks<2, 2, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
-    case 3: return launch_ks<3, 2, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
-    case 4: return launch_ks<2, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
-    case 5: return launch_ks<3, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
-    case 6: return launch_ks<4, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
-    case 7: return launch_ks<big ? 5 : 4, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
-    case 8: return launch_ks<big ? 6 : 4, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
-    case 9: return launch_ks<big ? 8 : 4, 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
-    case 10: return launch_ks<4, big ? 5 : 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
-    case 11: return launch_ks<big ? 5 : 4, big ? 5 : 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
-    case 12: return launch_ks<4, big ? 6 : 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
-    case 13: return launch_ks<big ? 5 : 4, big ? 6 : 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
-    default: return launch_ks<big ? 6 : 4, big ? 6 : 4, 4, WF>(M, N, K, X, w, Y, y_bf16, stream);
-  }
+  if constexpr (I + 1 < kKsConfigs)
+    if (cfg != I) return launch_ks_config<WF, I + 1>(cfg, M, N, K, X, w, Y, y_bf16, stream);
+  constexpr KsTile t = kKsTiles[I];
+  return launch_ks<t.mt, t.nt, t.waves, WF>(M, N, K, X, w, Y, y_bf16, stream);
 }
 
 // One region of a plan, an ordinary smaller problem.
@@ -2757,6 +2805,26 @@ static q4nx_status check_launch(const char* fn) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(Q4NX_ERR_HIP, std::string(fn) + ": " + hipGetErrorString(e));
   return Q4NX_OK;
+}
+
+// The kernels that a choice runs, as launch_wide and launch_region pick them.
+static std::string launches_text(const GemmChoice& c, int wf, int64_t K) {
+  const auto size = [](int m, int n) { return std::to_string(m) + "x" + std::to_string(n); };
+  const auto wide = [&](int tile) {
+    const WideTile& t = kWideTiles[tile];
+    return (tile == kWideSquare && K >= kSquareLongK ? "gemm256 " : "tile ") + size(64 * t.ti, 64 * t.tj);
+  };
+  if (c.ks >= 0) return "ks " + size(16 * kKsTiles[c.ks].mt, 16 * kKsTiles[c.ks].nt);
+  std::string s = wf == kWQ4NX && c.two_phase ? "dequant" : "";
+  const auto add = [&](const std::string& l) { s += (s.empty() ? "" : " + ") + l; };
+  for (int i = 0; i < c.wide_count; ++i) add(wide(c.wide[i].tile));
+  for (int i = 0; c.wide_count == 0 && i < c.count; ++i) {
+    const GemmRegion& r = c.plan[i];
+    if (r.ks > 1) add("split" + std::to_string(r.ks) + " 256x256");
+    else if (wide_ok(K)) add(wide(kPlanWide[r.tile]));
+    else add((r.tile == 0 && K < kWideMaxK ? "gemm256 " : "general ") + size(kGemmTiles[r.tile].bm, kGemmTiles[r.tile].bn));
+  }
+  return s;
 }
 
 // Row-group size: whole strips when there are enough of them to keep at least
@@ -3007,6 +3075,17 @@ q4nx_status q4nx_mx_gemm(int64_t M, int64_t N, int64_t K, const uint16_t* d_X, c
 q4nx_status q4nx_gemm_bf16(int64_t M, int64_t N, int64_t K, const uint16_t* d_X, const uint16_t* d_W, void* d_Y,
                            q4nx_dtype y_dtype, hipStream_t stream) {
   return gemm_entry<kWBf16>(M, N, K, d_X, d_W, d_Y, y_dtype, nullptr, 0, stream, "q4nx_gemm_bf16");
+}
+
+int q4nx_internal_gemm_launches(int w_format, int64_t M, int64_t N, int64_t K, int have_work, char* text, int size) {
+  if (!text || size <= 0 || M <= 0 || M > Q4NX_MAX_DIM || check_shape(N, K, "q4nx_internal_gemm_launches") != Q4NX_OK ||
+      M * N > (int64_t(1) << 40) || w_format < Q4NX_WEIGHTS_Q4NX || w_format > Q4NX_WEIGHTS_BF16)
+    return -1;
+  const int wf = w_format == Q4NX_WEIGHTS_Q4NX ? kWQ4NX : w_format == Q4NX_WEIGHTS_MXFP4 ? kWMX : kWBf16;
+  const std::string s = launches_text(gemm_choose(wf, M, N, K, have_work != 0), wf, K);
+  if ((int)s.size() >= size) return -1;
+  std::copy(s.c_str(), s.c_str() + s.size() + 1, text);
+  return (int)s.size();
 }
 
 size_t q4nx_gemm_workspace_size(q4nx_weights w_format, int64_t M, int64_t N, int64_t K) {

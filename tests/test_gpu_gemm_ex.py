@@ -277,20 +277,26 @@ def test_gemm_ex_split_repeats_with_workspace_cleared(q4):
     assert all(torch.equal(y.view(torch.int32), ref.view(torch.int32)) for y in outs)
 
 
-# One shape per tile of the kernel that splits K over a workgroup's waves
-# (q4nx_gemm's choice for few rows on a 256-CU device), each with ragged M and
-# N (the last tile of either may hold a few rows or outputs, N not a multiple
-# of a strip) and a K that ends inside a 128-column unit; then K of one group,
-# one unit, and many units.
+# The kernel that splits K over a workgroup's waves (q4nx_gemm's choice for few
+# rows on a 256-CU device): ragged N (not a multiple of a strip) and mostly a
+# ragged M, K that ends inside a 128-column unit, K of one group, one unit, and
+# many units.
 FEW_ROWS = [(16, 100, 1184), (1, 6001, 1184), (34, 3001, 1184), (47, 6001, 1184), (145, 2501, 1184),
             (67, 8001, 1184), (193, 4001, 1184), (145, 6001, 1184), (163, 6001, 1184), (193, 6001, 1184),
             (3, 40, 32), (17, 33, 128), (77, 2560, 10272),
             # the tiles of 80 x 64, 128 x 64 and those of 80 and 96 columns, K ending inside a unit
             (65, 12001, 672), (110, 15001, 1184), (49, 18001, 672), (65, 18001, 672), (49, 24001, 672), (65, 24001, 672),
             (163, 10001, 672)]
+# One shape per tile (test_gemm_launches.py checks that they reach it), with several ragged tiles in
+# either direction and K ending inside a unit.
+FEW_ROWS_TILES = [(18, 35, 320, "16x16"), (20, 2101, 416, "16x32"), (68, 847, 288, "32x32"), (101, 2203, 288, "48x32"),
+                  (105, 3551, 288, "32x64"), (66, 7535, 544, "48x64"), (421, 2199, 416, "64x64"),
+                  (130, 7597, 480, "80x64"), (247, 4177, 608, "96x64"), (435, 4089, 1312, "128x64"),
+                  (97, 8427, 736, "64x80"), (133, 9891, 736, "80x80"), (217, 5523, 864, "64x96"),
+                  (258, 5719, 352, "80x96"), (175, 8353, 736, "96x96")]
 
 
-@pytest.mark.parametrize("M,N,K", FEW_ROWS)
+@pytest.mark.parametrize("M,N,K", FEW_ROWS + [shape[:3] for shape in FEW_ROWS_TILES])
 def test_gemm_few_rows(q4, M, N, K):
     """Float32 and bf16 outputs against the float64 product of the bf16
     weights (within 1e-5 of sum |x w|: float32 sums of exact products, over
