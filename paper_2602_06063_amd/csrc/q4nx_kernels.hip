@@ -2413,6 +2413,20 @@ constexpr int kWideConfigs = (int)(sizeof(kWideTiles) / sizeof(kWideTiles[0]));
 constexpr int kWideSquare = kWideConfigs - 1;  // 256 x 256
 constexpr int kPlanWide[4] = {kWideSquare, 3, 1, 0};  // what computes a region of a plan, by its tile
 constexpr int64_t kSquareLongK = 4096;
+// Up to 448 columns of K the general kernel computes the 128 and 256 column
+// tiles of two to four row blocks: gemm_tile_kernel's one wave per SIMD has too
+// few steps to earn its longer start and end.  Measured on MI355X, gemm_tile_kernel
+// against the general kernel (us, Q4NX and bf16 weights): 480 x 13328 x 64 12.6
+// and 12.1 against 8.1 and 9.0, 272 x 9908 x 64 7.3 and 6.8 against 6.1 and 5.4,
+// 741 x 7685 x 256 12.7 and 11.9 against 11.0 and 11.3, 1569 x 1451 x 384 10.1 and 9.1
+// against 9.2 and 8.2, 1835 x 1257 x 448 10.8 and 9.5 against 10.2 and 8.9; level at K =
+// 704 (384 x 5631).  The 64 x 128 tile and the larger ones stay ahead (339 x 4798
+// x 128 5.6 against 6.1, 1266 x 8017 x 192 17.4 against 25.6).
+constexpr int64_t kTileShortK = 512;
+static int short_k_tile(int wide_tile, int64_t K) {  // tile of kGemmTiles, or -1: gemm_tile_kernel's own
+  if (K >= kTileShortK || wide_tile < 1 || wide_tile > 3) return -1;
+  return wide_tile == 1 ? 2 : 1;
+}
 // K that gemm_tile_kernel takes: whole steps, and 320 rows of X below 2^31 bytes.
 static bool wide_ok(int64_t K) { return K % kBK == 0 && K < kWideMaxK / 2; }
 constexpr double kExtraLaunchUs = 2.0;
@@ -2662,10 +2676,35 @@ static void region_operands(int64_t m0, int64_t n0, int64_t N, int64_t K, int y_
   Y = static_cast<uint8_t*>(Y) + (m0 * N + n0) * (y_bf16 ? 2 : 4);
 }
 
+// The product by the general kernel with a tile of kGemmTiles (256 x 256:
+// gemm256_kernel's K tail form, up to its range).
+template <int WF>
+static q4nx_status launch_general(int tile, int64_t M, int64_t N, int64_t K, const uint16_t* X, const void* w, void* Y,
+                                  int64_t ldy, int y_bf16, hipStream_t stream) {
+  switch (tile) {
+    case 0:
+      if (K >= kWideMaxK) return launch_gemm<256, 256, 2, 4, WF>(M, N, K, X, w, Y, ldy, y_bf16, stream);
+      return launch_gemm256<true, WF>(M, N, K, X, w, Y, ldy, y_bf16, stream);
+    case 1:
+      // Q4NX weights as 16 waves of 32 x 64 (four per SIMD), which hide the
+      // dequantization in the tile loads better than 8 waves of 64 x 64
+      // (measured on MI355X: Gemma3 4B q/k/v 56.8 -> 55.5 us, o 42.2 -> 39.2 us
+      // with K a multiple of 64); bf16 and MXFP4-variant weights keep 8 waves
+      // (the 4B bf16 gate/up remainder ran 2.6% slower with 16).  Same MFMA
+      // chains, same bits.
+      if constexpr (WF == kWQ4NX) return launch_gemm<256, 128, 8, 2, WF>(M, N, K, X, w, Y, ldy, y_bf16, stream);
+      else return launch_gemm<256, 128, 4, 2, WF>(M, N, K, X, w, Y, ldy, y_bf16, stream);
+    case 2: return launch_gemm<128, 128, 2, 4, WF>(M, N, K, X, w, Y, ldy, y_bf16, stream);
+    default: return launch_gemm<128, 64, 2, 2, WF>(M, N, K, X, w, Y, ldy, y_bf16, stream);
+  }
+}
+
 template <int WF>
 static q4nx_status launch_wide(const WideRegion& r, int64_t N, int64_t K, const uint16_t* X, const void* w, void* Y,
                                int y_bf16, hipStream_t stream) {
   region_operands<WF>(r.m0, r.n0, N, K, y_bf16, X, w, Y);
+  if (const int t = short_k_tile(r.tile, K); t >= 0)
+    return launch_general<WF>(t, r.M, r.N, K, X, w, Y, N, y_bf16, stream);
   switch (r.tile) {
     case 0: return launch_tile<1, 2, WF>(r.M, r.N, K, X, w, Y, N, y_bf16, stream);
     case 1: return launch_tile<2, 2, WF>(r.M, r.N, K, X, w, Y, N, y_bf16, stream);
@@ -2731,22 +2770,7 @@ static q4nx_status launch_region(const GemmRegion& r, int64_t N, int64_t K, cons
                        (int)r.M, (int)r.N, Yr, N, y_bf16, vec);
     return Q4NX_OK;
   }
-  switch (r.tile) {
-    case 0:
-      if (K >= kWideMaxK) return launch_gemm<256, 256, 2, 4, WF>(r.M, r.N, K, Xr, Wr, Yr, N, y_bf16, stream);
-      return launch_gemm256<true, WF>(r.M, r.N, K, Xr, Wr, Yr, N, y_bf16, stream);
-    case 1:
-      // Q4NX weights as 16 waves of 32 x 64 (four per SIMD), which hide the
-      // dequantization in the tile loads better than 8 waves of 64 x 64
-      // (measured on MI355X: Gemma3 4B q/k/v 56.8 -> 55.5 us, o 42.2 -> 39.2 us
-      // with K a multiple of 64); bf16 and MXFP4-variant weights keep 8 waves
-      // (the 4B bf16 gate/up remainder ran 2.6% slower with 16).  Same MFMA
-      // chains, same bits.
-      if constexpr (WF == kWQ4NX) return launch_gemm<256, 128, 8, 2, WF>(r.M, r.N, K, Xr, Wr, Yr, N, y_bf16, stream);
-      else return launch_gemm<256, 128, 4, 2, WF>(r.M, r.N, K, Xr, Wr, Yr, N, y_bf16, stream);
-    case 2: return launch_gemm<128, 128, 2, 4, WF>(r.M, r.N, K, Xr, Wr, Yr, N, y_bf16, stream);
-    default: return launch_gemm<128, 64, 2, 2, WF>(r.M, r.N, K, Xr, Wr, Yr, N, y_bf16, stream);
-  }
+  return launch_general<WF>(r.tile, r.M, r.N, K, Xr, Wr, Yr, N, y_bf16, stream);
 }
 
 // The launches of gemm_tile_kernel, or the plan's.
@@ -2812,6 +2836,7 @@ static std::string launches_text(const GemmChoice& c, int wf, int64_t K) {
   const auto size = [](int m, int n) { return std::to_string(m) + "x" + std::to_string(n); };
   const auto wide = [&](int tile) {
     const WideTile& t = kWideTiles[tile];
+    if (const int g = short_k_tile(tile, K); g >= 0) return "general " + size(kGemmTiles[g].bm, kGemmTiles[g].bn);
     return (tile == kWideSquare && K >= kSquareLongK ? "gemm256 " : "tile ") + size(64 * t.ti, 64 * t.tj);
   };
   if (c.ks >= 0) return "ks " + size(16 * kKsTiles[c.ks].mt, 16 * kKsTiles[c.ks].nt);

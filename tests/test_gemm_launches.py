@@ -4,7 +4,7 @@ there for."""
 import pytest
 
 from gemm_launches import FORMATS, launches
-from test_gpu_gemm_ex import FEW_ROWS_TILES
+from test_gpu_gemm_ex import FEW_ROWS_TILES, SHORT_K
 
 
 @pytest.mark.parametrize("M,N,K,tile", FEW_ROWS_TILES)
@@ -32,3 +32,15 @@ def test_few_rows_tiles_refused_where_bf16_weights_lose(M, N, K):
 def test_few_rows_tiles_taken(M, N, K):
     for f in FORMATS:
         assert launches(f, M, N, K).startswith("ks")
+
+
+@pytest.mark.parametrize("M,N,K,tile", SHORT_K)
+def test_short_k_takes_the_general_kernel(M, N, K, tile):
+    """gemm_tile_kernel takes up to 1.5 times as long there."""
+    assert [launches(f, M, N, K) for f in FORMATS] == ["general " + tile] * 3
+
+
+@pytest.mark.parametrize("M,N,K", [(339, 4798, 128), (1266, 8017, 192), (384, 5631, 704)])
+def test_other_tiles_and_longer_k_do_not(M, N, K):
+    for f in FORMATS:
+        assert launches(f, M, N, K).startswith("tile")

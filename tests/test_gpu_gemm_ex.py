@@ -341,7 +341,13 @@ TILE_SHAPES = [(80, 5000, 64), (80, 20001, 64), (140, 20001, 64), (200, 20001, 6
                (520, 30001, 64), (580, 30001, 64), (400, 43001, 192), (1999, 20001, 192)]
 
 
-@pytest.mark.parametrize("M,N,K", TILE_SHAPES)
+# K of at most 448, a multiple of 64: the general kernel's 128 and 256 row tiles (test_gemm_launches.py
+# checks that they reach it), of one, two, four and seven steps.
+SHORT_K = [(272, 9909, 64, "128x128"), (504, 12417, 128, "256x128"), (741, 7685, 256, "256x128"),
+           (1835, 1257, 448, "128x128")]
+
+
+@pytest.mark.parametrize("M,N,K", TILE_SHAPES + [shape[:3] for shape in SHORT_K])
 def test_gemm_tiles(q4, M, N, K):
     """Sampled rows against the float64 product of the bf16 weights within the
     tight bound, every element (packed, MXFP4 and bf16 weights, float32 and
