@@ -4,7 +4,7 @@ there for."""
 import pytest
 
 from gemm_launches import FORMATS, launches
-from test_gpu_gemm_ex import FEW_ROWS_TILES, SHORT_K
+from test_gpu_gemm_ex import FEW_ROWS_TILES, K_TAILS, LONG_K_SHAPES, SHORT_K, SPLIT_SHAPES, TILE_STEPS
 
 
 @pytest.mark.parametrize("M,N,K,tile", FEW_ROWS_TILES)
@@ -44,3 +44,34 @@ def test_short_k_takes_the_general_kernel(M, N, K, tile):
 def test_other_tiles_and_longer_k_do_not(M, N, K):
     for f in FORMATS:
         assert launches(f, M, N, K).startswith("tile")
+
+
+def test_every_tile_has_shapes_of_odd_and_even_steps():
+    """All ten tiles with each of the three operands, ragged in M and N, over
+    2 D + 1 steps or more (D register sets: 4 of the 64 x 128 tile, else 2)."""
+    seen = set()
+    for M, N, K in TILE_STEPS:
+        for f in FORMATS:
+            tile = launches(f, M, N, K)
+            assert tile.startswith("tile ") and "+" not in tile
+            bm, bn = map(int, tile[5:].split("x"))
+            assert M % bm and N % bn and N % 32
+            assert K // 64 >= (9 if (bm, bn) == (64, 128) else 5)
+            seen.add((f, tile, K // 64 % 2))
+    assert len(seen) == 10 * 3 * 2
+
+
+@pytest.mark.parametrize("M,N,K,text", K_TAILS)
+def test_k_tails_reach_the_general_tiles(M, N, K, text):
+    assert [launches(f, M, N, K) for f in FORMATS] == [text] * 3
+
+
+def test_split_shapes_split():
+    segments = set()
+    for M, N, K, _ in SPLIT_SHAPES:
+        texts = [launches(f, M, N, K, work=True) for f in FORMATS]
+        assert all("split" in t for t in texts)
+        segments.add((texts[1].split()[0], K % 64 == 0, M % 256 == 0))
+    assert {(f"split{k}", whole, False) for k in (2, 3, 4) for whole in (False, True)} <= segments
+    for M, N, K, _ in LONG_K_SHAPES:
+        assert all("split" not in launches(f, M, N, K, work=True) for f in FORMATS)

@@ -1,8 +1,9 @@
 """q4nx_gemm_ex through the C ABI: the matrix product with a caller workspace,
 where the launch plan splits K for shapes with few output tiles.
 
-  * every case here takes a split plan (q4nx_gemm_workspace_size > 0), with
-    ragged M and N, K not a multiple of 64, float32 and bf16 outputs;
+  * SPLIT_SHAPES take a plan that splits K into two, three or four segments
+    (checked against the planner), with ragged M and N, K not a multiple of 64,
+    float32 and bf16 outputs;
   * parity with the float64 oracle: the projection tolerance and the tight
     bound against the product of the bf16 weights;
   * the three weight formats give the same bits for the same bf16 weights
@@ -17,6 +18,7 @@ import numpy as np
 import pytest
 
 import oracle
+from gemm_launches import FORMATS, launches
 from workloads import gen_weights, gen_mx_weights, gen_activations
 
 torch = pytest.importorskip("torch")
@@ -63,9 +65,15 @@ def work_if_any(q4, M, N, K, fmt):
     return torch.full((nbytes // 4,), float("nan"), dtype=torch.float32, device="cuda") if nbytes else None
 
 
-# (M, N, K, rows checked by the oracle: None = all)
-SPLIT_SHAPES = [(512, 512, 16384, None), (512, 512, 16352, None), (300, 520, 20000, None), (260, 257, 12000, None),
-                (1, 256, 20480, None), (2048, 2560, 10240, 64), (2048, 2560, 10208, 64), (4096, 5376, 21504, 48)]
+# (M, N, K, rows checked by the oracle: None = all).  The last six: ragged
+# tiles at the edges of a split, and outputs that the sum of the segments takes
+# one by one (N not a multiple of 4).
+SPLIT_SHAPES = [(2048, 2560, 10240, 64), (2048, 2560, 10208, 64), (4096, 5376, 21504, 48), (700, 3333, 6912, 48),
+                (394, 5145, 5472, 48), (1540, 2447, 4928, 48), (1291, 2987, 4832, 48), (827, 5455, 7296, 48),
+                (859, 5399, 7264, 48)]
+# A long K that one launch takes, with the workspace at hand.
+LONG_K_SHAPES = [(512, 512, 16384, None), (512, 512, 16352, None), (300, 520, 20000, None), (260, 257, 12000, None),
+                 (1, 256, 20480, None)]
 
 
 def _rows(M, n):
@@ -75,9 +83,10 @@ def _rows(M, n):
     return np.unique(np.concatenate([np.arange(8), M - 8 + np.arange(8), rng.integers(0, M, n)]))
 
 
-@pytest.mark.parametrize("M,N,K,nrows", SPLIT_SHAPES)
+@pytest.mark.parametrize("M,N,K,nrows", SPLIT_SHAPES + LONG_K_SHAPES)
 @pytest.mark.parametrize("bf16_out", [False, True])
 def test_gemm_ex_split_parity(q4, M, N, K, nrows, bf16_out):
+    assert ("split" in launches(q4.Q4NX_WEIGHTS_Q4NX, M, N, K, work=True)) == ((M, N, K, nrows) in SPLIT_SHAPES)
     _say("gemm_ex split", M, N, K, "bf16" if bf16_out else "f32")
     codes, s, o = gen_weights(N, K, seed=M + K)
     blob = dev_u8(q4.q4nx_pack(codes, s, o))
@@ -98,10 +107,13 @@ def test_gemm_ex_split_parity(q4, M, N, K, nrows, bf16_out):
     assert tight.all()
 
 
-@pytest.mark.parametrize("M,N,K", [(300, 520, 20000), (260, 257, 12000), (2048, 2560, 10208)])
-def test_gemm_ex_formats_agree_bitwise(q4, M, N, K):
+@pytest.mark.parametrize("M,N,K,split", [(300, 520, 20000, False), (260, 257, 12000, False), (2048, 2560, 10208, True),
+                                         (700, 3333, 6912, True), (394, 5145, 5472, True)])
+def test_gemm_ex_formats_agree_bitwise(q4, M, N, K, split):
     """Q4NX and MXFP4-variant blobs against the bf16 weights they dequantize
-    to, all through split plans: identical bits."""
+    to, through split plans or with the workspace unused: identical bits."""
+    for f in FORMATS:
+        assert ("split" in launches(f, M, N, K, work=True)) == split
     _say("gemm_ex formats", M, N, K)
     X = dev_bf16(gen_activations((M, K), seed=M))
     work = work_for(q4, M, N, K)
@@ -131,7 +143,9 @@ def test_gemm_ex_formats_agree_bitwise(q4, M, N, K):
 
 
 def test_gemm_ex_repeatable_and_unsplit_without_workspace(q4):
-    M, N, K = 512, 512, 16352
+    M, N, K = 700, 3333, 6944
+    assert "split" in launches(q4.Q4NX_WEIGHTS_Q4NX, M, N, K, work=True)
+    assert "split" not in launches(q4.Q4NX_WEIGHTS_Q4NX, M, N, K)
     _say("gemm_ex repeat / no workspace", M, N, K)
     codes, s, o = gen_weights(N, K, seed=9)
     blob = dev_u8(q4.q4nx_pack(codes, s, o))
@@ -183,16 +197,12 @@ def test_gemm_ex_dequantize_then_multiply(q4, M, N, K, split):
     assert ok, worst
 
 
-# Shapes whose tiles do not fill whole rounds of the 256 CUs, where the plan
-# mixes tile shapes or splits K: a round and a few tiles (4352 x 4096), two
-# rounds and a part (4352 x 8448), the Gemma3-4B o shape (80 tiles), few tiles
-# over a long K with M and N ragged (2000 x 1100 x 6912), and a K tail with a
-# ragged M (1999 x 2500 x 2016).
-# Ragged prefill-sized shapes; the planner takes a different plan for each:
-# dequantize-once with a partial last wave of tiles (the first two), the
-# direct fused launch (the third and fifth), split K (the fourth), and one
-# round of 256 x 128 tiles with M and N ragged (the sixth and seventh, N a
-# multiple of 32 or not: the one-wave-per-SIMD 256 x 128 kernel's edge tiles).
+# Shapes whose tiles do not fill whole rounds of the 256 CUs: a round and a few
+# tiles (4352 x 4096), two rounds and a part (4352 x 8448), the Gemma3-4B o
+# shape (80 tiles), few tiles over a long K with M and N ragged (2000 x 1100 x
+# 6912: the few-rows kernel), a K tail with a ragged M (1999 x 2500 x 2016), and
+# M and N ragged with N a multiple of 32 or not (2040 x 4000 and 3999).  The
+# first two dequantize once.
 PLANNED_SHAPES = [(4352, 4096, 2560, 32), (4352, 8448, 2560, 32), (2048, 2560, 2048, 48), (2000, 1100, 6912, 48),
                   (1999, 2500, 2016, 48), (2040, 4000, 2560, 48), (2040, 3999, 2560, 48)]
 
@@ -253,7 +263,8 @@ def test_gemm_ex_split_repeats_with_workspace_cleared(q4):
     """Ten calls of a split-K plan in a row, the workspace refilled with NaN
     before each: a partial read before its writer finished, or one left over
     from the previous call, would show as a NaN or a changed bit."""
-    M, N, K = 2000, 1100, 6912
+    M, N, K = 700, 3333, 6912
+    assert "split" in launches(q4.Q4NX_WEIGHTS_Q4NX, M, N, K, work=True)
     _say("gemm_ex split repeats", M, N, K)
     codes, s, o = gen_weights(N, K, seed=77)
     blob = dev_u8(q4.q4nx_pack(codes, s, o))
@@ -331,11 +342,9 @@ def test_gemm_few_rows(q4, M, N, K):
     assert torch.equal(Y[0].view(torch.int32), Y[1].view(torch.int32))
 
 
-# One shape per tile of the hand-scheduled kernel (and two launches over a
-# split of the rows or the columns), as q4nx_gemm chooses them on a 256-CU
-# device for Q4NX weights: ragged M and N throughout, K of one, two, three and
-# five steps.  (Other weights may take other tiles; every tile sums in the
-# same order.)
+# The hand-scheduled kernel and the general one, one launch or two over a split
+# of the rows or the columns: ragged M and N throughout, K of one, two, three
+# and five steps.
 TILE_SHAPES = [(80, 5000, 64), (80, 20001, 64), (140, 20001, 64), (200, 20001, 64), (60, 43001, 64),
                (260, 30001, 64), (400, 20001, 128), (140, 43001, 64), (260, 43001, 192), (580, 20001, 320),
                (520, 30001, 64), (580, 30001, 64), (400, 43001, 192), (1999, 20001, 192)]
@@ -345,9 +354,20 @@ TILE_SHAPES = [(80, 5000, 64), (80, 20001, 64), (140, 20001, 64), (200, 20001, 6
 # checks that they reach it), of one, two, four and seven steps.
 SHORT_K = [(272, 9909, 64, "128x128"), (504, 12417, 128, "256x128"), (741, 7685, 256, "256x128"),
            (1835, 1257, 448, "128x128")]
+# Each tile of the hand-scheduled kernel with each weight operand (the packed and the other operands may
+# take another tile at a shape), over an odd and an even number of steps that takes every register set
+# around at least twice; and the general kernel's tiles with a K tail, of several steps.
+TILE_STEPS = [(33, 8213, 576), (33, 11403, 640), (33, 33813, 320), (33, 33351, 384), (67, 16387, 576), (66, 16457, 640),
+              (129, 16571, 576), (130, 16899, 640), (129, 33057, 320), (131, 32775, 384), (257, 21929, 320),
+              (258, 22457, 384), (194, 16599, 576), (193, 16701, 640), (257, 33027, 320), (257, 34171, 384),
+              (387, 24609, 320), (386, 24615, 384), (323, 24947, 320), (323, 24613, 384), (193, 32825, 320),
+              (195, 33139, 384)]
+K_TAILS = [(66, 11059, 288, "general 128x64"), (33, 28325, 288, "general 128x128"),
+           (134, 16407, 352, "general 256x128"), (260, 17547, 288, "gemm256 256x256"),
+           (84, 36249, 352, "general 128x128 + general 128x64")]
 
 
-@pytest.mark.parametrize("M,N,K", TILE_SHAPES + [shape[:3] for shape in SHORT_K])
+@pytest.mark.parametrize("M,N,K", TILE_SHAPES + TILE_STEPS + [shape[:3] for shape in SHORT_K + K_TAILS])
 def test_gemm_tiles(q4, M, N, K):
     """Sampled rows against the float64 product of the bf16 weights within the
     tight bound, every element (packed, MXFP4 and bf16 weights, float32 and
