@@ -188,7 +188,11 @@ q4nx_status q4nx_gemv_batched(const q4nx_gemv_desc* descs, int32_t count, q4nx_d
  * Device.  Prefill projection (Sec. 3.1.2, C = A x B with A = X, B = W^T):
  * Y[m][n] = sum_k X[m][k] * w[n][k], where each weight is dequantized with
  * Eq. 3 and rounded to bf16 (the paper dequantizes to bf16 before its MM),
- * the products are bf16 x bf16 on the matrix cores and the sums are float32.
+ * the products are bf16 x bf16 on the matrix cores and the sums are float32,
+ * over K in an order fixed by M, N and K: the same call gives the same bits
+ * every time, but a row computed in a batch of another M may differ from it in
+ * the last bits (products of few rows add four or eight partial sums, others one
+ * chain).
  *   d_X : device, row-major [M][K] bf16, 16-byte aligned, K*2 % 16 == 0
  *         holds because K % 32 == 0
  *   d_blob : device, packed N x K matrix, 16-byte aligned
@@ -299,7 +303,9 @@ q4nx_status q4nx_flowkv_decode_static(const uint16_t* d_q, const uint16_t* d_k, 
  * product.  For Q4NX weights and a large M it may also dequantize W to bf16
  * in the workspace first (each weight once instead of once per row of output
  * tiles) and run the same plan on those weights, which gives the same bits as
- * the fused kernel.  With d_work == NULL nothing is split or staged and the
+ * the fused kernel.  The order of the sums is fixed by M, N, K and whether
+ * there is a workspace, and is the same for the three weight operands.  With
+ * d_work == NULL nothing is split or staged and the
  * result equals the matching entry point's bit for bit.  Errors: as
  * q4nx_gemm; Q4NX_ERR_BUFFER_TOO_SMALL if work_bytes is below the need.
  */
@@ -311,8 +317,11 @@ typedef enum q4nx_weights {
   Q4NX_WEIGHTS_RANGE_MAX_ = 2147483647
 } q4nx_weights;
 
-/* Bytes of workspace q4nx_gemm_ex may use for (w_format, M, N, K) on the
- * current device (0 when it would use none, or if an argument is invalid). */
+/* Bytes of workspace that q4nx_gemm_ex asks for with (w_format, M, N, K) on
+ * the current device: what its plan of tiles may use.  Some products that ask
+ * for one then run in a launch that leaves it untouched; the size is required
+ * all the same where a workspace is passed.  0 when the plan uses none, or if
+ * an argument is invalid. */
 size_t q4nx_gemm_workspace_size(q4nx_weights w_format, int64_t M, int64_t N, int64_t K);
 
 q4nx_status q4nx_gemm_ex(q4nx_weights w_format, int64_t M, int64_t N, int64_t K, const uint16_t* d_X,
@@ -363,7 +372,7 @@ q4nx_status q4nx_mx_gemv(const void* d_blob, const uint16_t* d_x, void* d_y, q4n
 q4nx_status q4nx_mx_gemv_batched(const q4nx_gemv_desc* descs, int32_t count, q4nx_dtype y_dtype,
                                  hipStream_t stream);
 
-/* Device: q4nx_gemm for an MXFP4-variant blob (the bf16 weights are exact). */
+/* Device: q4nx_gemm for an MXFP4-variant blob (the bf16 weights are exact; the sums in the order of q4nx_gemm). */
 q4nx_status q4nx_mx_gemm(int64_t M, int64_t N, int64_t K, const uint16_t* d_X, const void* d_blob, void* d_Y,
                          q4nx_dtype y_dtype, hipStream_t stream);
 
