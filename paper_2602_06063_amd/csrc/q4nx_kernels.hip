@@ -1429,7 +1429,7 @@ __global__ __launch_bounds__(kWideThreads) void gemm256_kernel(const uint16_t* _
 // 166 (320 x 192; MXFP4 weights 220 -> 147), 512 rows of 4B gate/up 73 -> 64
 // (256 x 192), 128 rows 41 -> 28 (128 x 128, a wave per SIMD instead of two
 // on the compiler's schedule), 512 rows of 4B q/k/v 37 -> 26 (64 x 128).  Tiles of 64 x 64, 128 x 64, 128 x 192
-// and 192 x 192 were never the best and are not built.
+// and 192 x 192 were nowhere ahead by more than 2% and are not built.
 template <int TI, int TJ, int WF>
 struct TileRegs {
   u32x4 x[2 * TI];
@@ -1955,7 +1955,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_kernel(
 // waves have loads in flight.
 // A unit of W (half a block) and of X go through the wave's own LDS slot:
 // loaded with whole 64-byte (codes) and 256-byte (X) row pieces, written with
-// padded rows (272 bytes for X, 80 for codes: conflict-free), and read back in
+// padded rows (272 bytes for X, 80 for codes), and read back in
 // the operand layout of v_mfma_f32_16x16x32_bf16: lane l holds row l % 16 and
 // group l / 16 of the unit, whose 8-column runs are the fragments of four
 // MFMAs.  (Loading the fragments straight from memory, 16 bytes per row and
@@ -1966,8 +1966,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_kernel(
 // Gemma3-1B at 16 rows q/k/v 14.7 -> 4.2, o 13.4 -> 4.0, gate/up 16.4 -> 7.1,
 // down 67.5 -> 9.0; 4B at 77 rows 29.0 -> 9.7, 23.9 -> 6.9, 41.5 -> 30.9,
 // 100 -> 18.4.  Whole calls through q4nx_gemm_ex: eight 1B layers at 16 rows
-// 869 -> 278 us (then bound by the caller), four 4B layers at 77 rows 816 ->
-// 269 us, two at 512 rows 541 -> 327 us.
+// 869 -> 181 us (then bound by the caller), four 4B layers at 77 rows 816 ->
+// 220 us, two at 512 rows 541 -> 301 us.
+// What bounds it: one wave per SIMD does a unit's LDS writes, fragment reads,
+// dequantization and MFMAs one after another.  Of a wave's cycles at 4B and 77
+// rows (counters; q/k/v, o and down, gate/up): VALU 28, 38 and 33%, MFMA 11, 12
+// and 19%, LDS instructions 11, 12 and 9% (28 to 31% of the LDS cycles are bank
+// conflicts), waiting for memory or LDS data 27, 25 and 18%, for the LDS queue 3
+// to 5%.
 // Tiles of 80 and 96 columns: an X fragment read and an X row staged serve more
 // outputs, and products of many columns take one round of tiles where 64 columns
 // needed two.  4B gate/up at 77 rows 31.1 -> 21.5 us, 27B gate/up at 77 rows 96
@@ -2266,13 +2272,10 @@ struct GemmRegion {
 // ~5 us launch.
 constexpr double kRoundFixedUs = 40.0, kRoundPerKUs = 0.0226;
 constexpr double kSumLaunchUs = 5.0, kSumBytesPerUs = 5.0e6;
-// (The round costs and this model were fitted before the buffer-store
-// epilogue took 6-10 us off every round.  A refit from single full rounds,
-// about 16 + 0.0237 K us and costs 1 : 0.65 : 0.40 : 0.32, picks worse plans
-// for partly filled launches -- e.g. a two-shape split of 4096 x 2560 x 2048
-// that runs 23% slower than one partial round of 256 x 256 tiles -- while
-// the plans chosen here measure within 2% of the best forced plan on every
-// Gemma3 prefill product, so they are kept.)
+// (The round costs and this model were fitted to kernels that compute few of
+// these tiles now.  They decide whether K is split, whether the weights are
+// dequantized first (timed again on the present kernels: below) and the
+// workspace a call asks for; other tiles compete by the times further down.)
 constexpr int kMinSegmentSteps = 8;
 
 static double round_us(int64_t K) { return kRoundFixedUs + kRoundPerKUs * (double)K; }
@@ -2373,16 +2376,19 @@ static size_t plan_work_bytes(const GemmRegion* plan, int count) {
 // W in bf16, a Q4NX product can dequantize each weight once instead (the
 // dequant kernel streams at ~5.5 TB/s) and run the same plan on the bf16
 // weights: the same bf16 values, the same MFMA chains and partial sums, so
-// the same bits.  The fused kernel's extra work is Eq. 3 inside the K loop:
-// measured on MI355X it adds about a fifth of the K-loop time of the
-// 256 x 256 kernel (1.19-1.26 x the bf16 product's time on the Gemma3 4B and
-// 27B products) and about a seventh for the smaller tiles of the general
-// kernel, so the two-phase route is taken when the dequantization pass is
-// estimated below that share of the planned K-loop time: every Gemma3 27B
-// product at M = 4096, the 4B gate/up and down products at M = 2048, not the
-// 4B q/k/v and o products (short K, smaller tiles) nor M <= 1024.  (The
-// MXFP4 variant's conversion is cheap enough that the fused kernel runs at
-// the bf16 speed.)
+// the same bits.  The fused kernel's extra work is Eq. 3 inside the K loop, so
+// the two-phase route is taken when the dequantization pass is estimated below
+// a share of the planned K-loop time: every Gemma3 27B product at M = 4096, the
+// 4B gate/up and down products at M = 2048, not the 4B q/k/v and o products.
+// (The MXFP4 variant's conversion is cheap enough that the fused kernel runs at
+// the bf16 speed.)  Measured on MI355X both ways over the eleven stacked Gemma3
+// products at M = 512 to 4096, 88 products: where it is taken the fused launches
+// take up to 1.15 times as long (us: 4096 x 43008 x 5376 1552 against 1793, 2048 x
+// 20480 x 2560 217 against 229, 2048 x 2560 x 10240 118 against 129), where it is
+// not the two phases take up to 1.36 times as long (4096 x 1536 x 1152 23.2
+// against 26.4, 1024 x 8192 x 5376 96 against 103); the wrong one is taken three
+// times, for 3 to 4% (1536 x 20480 x 2560 172 against 165, 1280 x 8192 x 5376 117
+// against 113, 1536 x 5376 x 21504 337 against 329).
 constexpr double kDequantLaunchUs = 3.0, kDequantBytesPerUs = 5.5e6;
 constexpr double kFusedExtraWide = 0.20, kFusedExtraSmall = 0.14;
 
@@ -2391,10 +2397,12 @@ constexpr double kFusedExtraWide = 0.20, kFusedExtraSmall = 0.14;
 // part of it is split along K; what runs is the cheapest of that plan, one or
 // two launches of gemm_tile_kernel, and one of gemm_ks_kernel, by the times
 // below.  They were fitted on MI355X to launches over K = 1152 .. 21504 and 40
-// to 640 tiles and predict those within about a tenth.  Which of the three runs
-// depends on M, N, K, the device and whether there is a workspace alone, so
-// the three weight operands always take the same sums; the tiles, which do not
-// change a bit, are chosen for the operand.
+// to 640 tiles and predict those within about a tenth (several full rounds of
+// 256 x 256 tiles with Q4NX weights take 1.2 times as long as with bf16 ones, where
+// the table has 1.1).  Which of the three runs depends on M, N, K, the device
+// and whether there is a workspace alone, so the three weight operands always
+// take the same sums; the tiles, which do not change a bit, are chosen for the
+// operand.
 
 // A full round of gemm_tile_kernel's tiles over K columns takes fixed_us +
 // slope K (slope_us: Q4NX weights dequantized in the K loop; bf16_us: the
@@ -2583,8 +2591,9 @@ struct GemmChoice {
   size_t part_bytes;  // split-K partial products after it
 };
 
-// (The workspace a call asks for is that of the plan, also where other
-// launches leave it unused: callers size and keep workspaces by it.)
+// (The workspace a call asks for is that of the plan, also where another launch
+// leaves it unused: whether there is one is part of the choice, so reporting 0
+// there would move a caller who then passes none to other sums.)
 static GemmChoice gemm_choose(int wf, int64_t M, int64_t N, int64_t K, bool have_work) {
   GemmChoice c{};
   double est_us = 0.0;
@@ -2688,10 +2697,10 @@ static q4nx_status launch_general(int tile, int64_t M, int64_t N, int64_t K, con
     case 1:
       // Q4NX weights as 16 waves of 32 x 64 (four per SIMD), which hide the
       // dequantization in the tile loads better than 8 waves of 64 x 64
-      // (measured on MI355X: Gemma3 4B q/k/v 56.8 -> 55.5 us, o 42.2 -> 39.2 us
-      // with K a multiple of 64); bf16 and MXFP4-variant weights keep 8 waves
-      // (the 4B bf16 gate/up remainder ran 2.6% slower with 16).  Same MFMA
-      // chains, same bits.
+      // (1999 x 2500 x 2016 40.3 -> 37.0 us, 261 x 13309 x 2208 40.3 -> 38.0, 741 x
+      // 7685 x 256 12.2 -> 11.1); bf16 and MXFP4-variant weights run 8, ahead for
+      // bf16 on 2040 x 3999 x 2592 (52.0 against 54.0) and 1 to 13% behind on the
+      // five other products timed.  Same MFMA chains, same bits.
       if constexpr (WF == kWQ4NX) return launch_gemm<256, 128, 8, 2, WF>(M, N, K, X, w, Y, ldy, y_bf16, stream);
       else return launch_gemm<256, 128, 4, 2, WF>(M, N, K, X, w, Y, ldy, y_bf16, stream);
     case 2: return launch_gemm<128, 128, 2, 4, WF>(M, N, K, X, w, Y, ldy, y_bf16, stream);
